@@ -149,7 +149,9 @@ int lbm_dirichlet_profile(lbm_ctx* ctx, int side, const double* d_U);
  * interval n > 0 set by lbm_diag_every, every step that brings the step count to a multiple of
  * n is followed by the diagnostics' non-finite count (one read of the populations, and the
  * call synchronises the stream there); when it is positive lbm_step stops and returns
- * LBM_E_NONFINITE, with the state of that step kept and lbm_steps_done telling which step. */
+ * LBM_E_NONFINITE, with the state of that step kept and lbm_steps_done telling which step.
+ * On large grids two steps are taken per pass over the populations (not across such a check);
+ * the result is that of single steps up to rounding. */
 int lbm_step(lbm_ctx* ctx, int nsteps);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving
@@ -201,7 +203,9 @@ long lbm_steps_done(const lbm_ctx* ctx);
 
 /* Kernel timing for measurement.  With enable = n > 0, lbm_step records a pair of HIP events
  * around every n-th step kernel launch (fused bulk stream-collide and boundary solve; the first
- * launch after this call is timed) on the caller's stream, resetting earlier records; 0 turns
+ * launch after this call is timed) on the caller's stream, resetting earlier records.  A pass of
+ * two steps (lbm_step) holds two of them: it is bracketed as a whole when one or both are to be
+ * timed, and each counts as one launch of half its time.  0 turns
  * timing off, a negative value returns LBM_E_ARG.  Each timed launch adds about 7 us of event
  * work to the stream, so a stride above 1 keeps a timed run's step rate close to an untimed
  * one.  lbm_bulk_kernel_time synchronises on the events and returns the summed elapsed

@@ -13,7 +13,8 @@
 // One time step n -> n+1 is one launch of k_step: its first work-groups each take a chunk of
 // rows of a boundary side (re-pull of the strip from A, RK4 of the characteristic system in
 // LDS, equilibrium populations of the M boundary layers of B); the remaining work-groups each
-// take 256 bulk nodes of one row (pull-stream + moments + equilibrium + BGK, A -> B).  Both
+// take 256 bulk nodes of one row (pull-stream + moments + equilibrium + BGK, A -> B).  On large
+// grids lbm_step takes two steps in one pass over memory instead (pair.h).  Both
 // kinds only read A and write disjoint nodes of B, so they need no ordering among themselves.
 // The boundary path's LDS (and registers) cap the launch at 2-3 work-groups per CU, which is
 // also the occupancy at which this many-stream access pattern streams fastest from HBM.
@@ -79,14 +80,17 @@ __device__ __forceinline__ void side_node(const SideDev& s, int k, int r, int& x
 }
 
 // ------------------------------------------------------------------ pull of one node (FP64)
+// populations of population i of node (x, y) at A[pix(pitch, i, x, y)]: the whole grid, or a band
+// buffer seen through a shifted pointer (View)
 template <int Q, typename T>
-__device__ __forceinline__ void pull_node(const T* __restrict__ A, const BndArgs& a, int x, int y, double* d) {
+__device__ __forceinline__ void pull_node(const T* __restrict__ A, unsigned long long pitch, const BndArgs& a, int x, int y,
+                                          double* d) {
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         int xs = x - cx<Q>(i), ys = y - cy<Q>(i);
         if (a.xper) xs = wrapi(xs, a.nx);
         if (a.yper) ys = wrapi(ys, a.ny);
-        d[i] = (double)A[pix<Q>(a.pitch, i, xs, ys)];
+        d[i] = (double)A[pix<Q>(pitch, i, xs, ys)];
     }
 }
 
@@ -560,12 +564,49 @@ __device__ __forceinline__ void corner_rate(const CornerDev& c, const double* Uc
     rate[3] = rl[3];
 }
 
-template <int Q, typename T>
-__device__ __forceinline__ void write_feq(T* __restrict__ B, unsigned long long pitch, int x, int y, const double* u4) {
+// Where a boundary work-group reads populations: population i of node (x, y) at
+// p[((y Q + i) pitch) + x] -- the whole grid, or the band buffer of a side (p shifted so that the
+// grid's coordinates index it).
+template <typename T> struct View {
+    const T* p;
+    unsigned long long pitch;
+};
+// ... and where it writes the layers (v(i): population i): the whole grid,
+template <typename T> struct GridDst {
+    T* B;
+    unsigned long long pitch;
+    template <int Q, typename F> __device__ __forceinline__ void put(int x, int y, F&& v) const {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) B[pix<Q>(pitch, i, x, y)] = (T)v(i);
+    }
+};
+// or the band buffers of one level: x-bands (the bw columns next to the sides x0 and x1: cx[..][cpx],
+// the low side at its start, the high side at its end) and y-bands (the bw rows next to y0, then those
+// next to y1); a node near a corner lies in both, a buffer that no side needs is NULL
+template <typename T> struct BandDst {
+    T *cx, *cy;
+    unsigned long long pitch;
+    int nx, ny, bw, cpx;
+    template <int Q, typename F> __device__ __forceinline__ void put(int x, int y, F&& v) const {
+        const bool xl = x < bw, xh = x >= nx - bw, yl = y < bw, yh = y >= ny - bw;
+        if (cx && (xl || xh)) {
+            T* o = cx + pix<Q>(cpx, 0, xl ? x : x - nx + cpx, y);
+#pragma unroll
+            for (int i = 0; i < Q; ++i) o[i * cpx] = (T)v(i);
+        }
+        if (cy && (yl || yh)) {
+            T* o = cy + pix<Q>(pitch, 0, x, yl ? y : y - ny + 2 * bw);
+#pragma unroll
+            for (int i = 0; i < Q; ++i) o[(unsigned long long)i * pitch] = (T)v(i);
+        }
+    }
+};
+
+template <int Q, typename D>
+__device__ __forceinline__ void write_feq(const D& B, int x, int y, const double* u4) {
     double fe[Q];
     feq_dev<Q, double>(u4[0] - 1.0, u4[1], u4[2], Lat<Q>::thermal ? u4[3] - 1.0 : 0.0, fe);
-#pragma unroll
-    for (int i = 0; i < Q; ++i) B[pix<Q>(pitch, i, x, y)] = (T)fe[i];
+    B.template put<Q>(x, y, [&](int i) { return fe[i]; });
 }
 
 // one corner: RK4 of the diagonal LODI system from the moments of the two inward diagonal nodes
@@ -666,8 +707,8 @@ template <int Q> struct ChunkShape {
     static constexpr int S = M + MS;        // normal slots per row
 };
 
-template <int Q, typename T, bool HIST>
-__device__ void char_chunk(const T* __restrict__ A, T* __restrict__ B, const BndArgs& a, const SideDev& sd, int chunk) {
+template <int Q, typename T, bool HIST, typename D>
+__device__ void char_chunk(const View<T> A, const D B, const BndArgs& a, const SideDev& sd, int chunk) {
     using CS = ChunkShape<Q>;
     constexpr int M = CS::M, MS = CS::MS, CR = CS::CR, NN = CS::NN, S = CS::S;
     constexpr bool TH = Lat<Q>::thermal;
@@ -760,7 +801,7 @@ __device__ void char_chunk(const T* __restrict__ A, T* __restrict__ B, const Bnd
         if (k < MS) {
             int x, y; side_node(sd, -k, rp, x, y);
             double d[Q];
-            pull_node<Q, T>(A, a, x, y, d);
+            pull_node<Q, T>(A.p, A.pitch, a, x, y, d);
             double u4[4];
             moments_u4<Q>(d, u4);
             if (owned) for (int m = 0; m < 4; ++m) stn[((size_t)k * len + rp) * 4 + m] = u4[m];
@@ -774,7 +815,7 @@ __device__ void char_chunk(const T* __restrict__ A, T* __restrict__ B, const Bnd
         double o6[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         if (bulk) {
             double d[Q];
-            pull_node<Q, T>(A, a, x, y, d);
+            pull_node<Q, T>(A.p, A.pitch, a, x, y, d);
             visc_moments<Q>(sd, d, a.tau, o6);
         }
         for (int m = 0; m < 6; ++m) visn[((size_t)kv * len + rp) * 6 + m] = o6[m];
@@ -784,7 +825,7 @@ __device__ void char_chunk(const T* __restrict__ A, T* __restrict__ B, const Bnd
         const int x = c.xc + ((tid & 1) + 1) * c.vx, y = c.yc + ((tid & 1) + 1) * c.vy;
         double d[Q];
 #pragma unroll
-        for (int i = 0; i < Q; ++i) d[i] = (double)A[pix<Q>(a.pitch, i, x - cx<Q>(i), y - cy<Q>(i))];
+        for (int i = 0; i < Q; ++i) d[i] = (double)A.p[pix<Q>(A.pitch, i, x - cx<Q>(i), y - cy<Q>(i))];
         moments_u4<Q>(d, sCp[tid >> 1][tid & 1]);
     }
     // stage-0 inputs: node values, strip at time n, corner values at time n in the corner rows
@@ -907,11 +948,11 @@ __device__ void char_chunk(const T* __restrict__ A, T* __restrict__ B, const Bnd
         for (int m = 0; m < 4; ++m) ubn[((size_t)jj * len + r) * 4 + m] = u4[m];
         int x, y; side_node(sd, jj + 1, r, x, y);
         if (sd.meso == 0) {   // equilibrium BC: all populations at equilibrium
-            write_feq<Q, T>(B, a.pitch, x, y, u4);
+            write_feq<Q>(B, x, y, u4);
         } else {              // eq. NEEP: plus the post-collision non-equilibrium part of x_f
             int xf, yf; side_node(sd, 0, r, xf, yf);
             double d[Q], fe[Q];
-            pull_node<Q, T>(A, a, xf, yf, d);
+            pull_node<Q, T>(A.p, A.pitch, a, xf, yf, d);
             double rm1, ux, uy, thv;
             moments_dev<Q, double>(d, rm1, ux, uy, thv);
             feq_dev<Q, double>(rm1, ux, uy, thv, fe);
@@ -919,8 +960,7 @@ __device__ void char_chunk(const T* __restrict__ A, T* __restrict__ B, const Bnd
 #pragma unroll
             for (int i = 0; i < Q; ++i) d[i] = c * (d[i] - fe[i]);
             feq_dev<Q, double>(u4[0] - 1.0, u4[1], u4[2], Lat<Q>::thermal ? u4[3] - 1.0 : 0.0, fe);
-#pragma unroll
-            for (int i = 0; i < Q; ++i) B[pix<Q>(a.pitch, i, x, y)] = (T)(fe[i] + d[i]);
+            B.template put<Q>(x, y, [&](int i) { return fe[i] + d[i]; });
         }
     }
     // the x-side's work-groups write the M x M corner blocks (fourth wavefront; the corner values
@@ -931,15 +971,15 @@ __device__ void char_chunk(const T* __restrict__ A, T* __restrict__ B, const Bnd
             const int e = u / (M * M), jx = (u / M) % M, jy = u % M;
             if (own_c[e]) {
                 const CornerDev c = pick_corner(cLo, cHi, e == 1);
-                write_feq<Q, T>(B, a.pitch, c.x0 + c.sxn * jx, c.y0 + c.syn * jy, sC[e][1]);
+                write_feq<Q>(B, c.x0 + c.sxn * jx, c.y0 + c.syn * jy, sC[e][1]);
             }
         }
     }
 }
 
 // ---------------------------------------------------------------- zero-gradient side (eq. zg-bc)
-template <int Q, typename T>
-__device__ void zg_chunk(const T* __restrict__ A, T* __restrict__ B, const BndArgs& a, const SideDev& sd, int chunk) {
+template <int Q, typename T, typename D>
+__device__ void zg_chunk(const View<T> A, const D B, const BndArgs& a, const SideDev& sd, int chunk) {
     constexpr int M = Lat<Q>::M;
     const T omega = sizeof(T) == 4 ? (T)(float)a.omega : (T)a.omega;
     const int r = chunk * sd.rows + threadIdx.x;
@@ -951,13 +991,12 @@ __device__ void zg_chunk(const T* __restrict__ A, T* __restrict__ B, const BndAr
             int xs = x - cx<Q>(i), ys = y - cy<Q>(i);
             if (a.xper) xs = wrapi(xs, a.nx);
             if (a.yper) ys = wrapi(ys, a.ny);
-            d[i] = A[pix<Q>(a.pitch, i, xs, ys)];
+            d[i] = A.p[pix<Q>(A.pitch, i, xs, ys)];
         }
         collide_dev<Q, T>(d, omega);
         for (int j = 1; j <= M; ++j) {
             int xb, yb; side_node(sd, j, r, xb, yb);
-#pragma unroll
-            for (int i = 0; i < Q; ++i) B[pix<Q>(a.pitch, i, xb, yb)] = d[i];
+            B.template put<Q>(xb, yb, [&](int i) { return d[i]; });
         }
     }
     // corner blocks copy the post-collision state of the inward diagonal node
@@ -972,27 +1011,24 @@ __device__ void zg_chunk(const T* __restrict__ A, T* __restrict__ B, const BndAr
 #pragma unroll
             for (int i = 0; i < Q; ++i) {
                 int xs = x - cx<Q>(i), ys = y - cy<Q>(i);
-                d[i] = A[pix<Q>(a.pitch, i, xs, ys)];
+                d[i] = A.p[pix<Q>(A.pitch, i, xs, ys)];
             }
             collide_dev<Q, T>(d, omega);
             for (int jx = 0; jx < M; ++jx)
-                for (int jy = 0; jy < M; ++jy) {
-#pragma unroll
-                    for (int i = 0; i < Q; ++i) B[pix<Q>(a.pitch, i, c.x0 + c.sxn * jx, c.y0 + c.syn * jy)] = d[i];
-                }
+                for (int jy = 0; jy < M; ++jy) B.template put<Q>(c.x0 + c.sxn * jx, c.y0 + c.syn * jy, [&](int i) { return d[i]; });
         }
     }
 }
 
-// one boundary work-group: find its side and chunk
-template <int Q, typename T, bool HIST>
-__device__ __forceinline__ void boundary_job(const T* __restrict__ A, T* __restrict__ B, const BndArgs& a, int b) {
+// one boundary work-group: find its side and chunk.  src(s): the View that side s reads
+template <int Q, typename T, bool HIST, typename S, typename D>
+__device__ __forceinline__ void boundary_job(S&& src, const D& B, const BndArgs& a, int b) {
     int s = 0;
     while (s < 4 && !(a.s[s].nblk > 0 && b >= a.s[s].blk0 && b < a.s[s].blk0 + a.s[s].nblk)) ++s;
     if (s == 4) return;
     const SideDev& sd = a.s[s];
-    if (sd.kind == KIND_CHAR) char_chunk<Q, T, HIST>(A, B, a, sd, b - sd.blk0);
-    else if (sd.kind == KIND_ZG) zg_chunk<Q, T>(A, B, a, sd, b - sd.blk0);
+    if (sd.kind == KIND_CHAR) char_chunk<Q, T, HIST>(src(s), B, a, sd, b - sd.blk0);
+    else if (sd.kind == KIND_ZG) zg_chunk<Q, T>(src(s), B, a, sd, b - sd.blk0);
 }
 
 // Waves per SIMD the step kernel is compiled for: 3 for D2Q37 in float (caps registers at 168
@@ -1013,7 +1049,7 @@ __global__ __launch_bounds__(256, (StepOcc<Q, T>::waves)) void k_step(const T* _
                                                                      BulkArgs g, int nbnd, int bpr, unsigned magic) {
     const int b = (int)blockIdx.x;
     if (b < nbnd) {
-        boundary_job<Q, T, HIST>(A, B, a, b);
+        boundary_job<Q, T, HIST>([&](int) { return View<T>{A, a.pitch}; }, GridDst<T>{B, a.pitch}, a, b);
         return;
     }
     unsigned t = (unsigned)(b - nbnd);

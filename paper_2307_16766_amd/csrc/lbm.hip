@@ -18,6 +18,7 @@
 #include "adjoint.h"
 #include "kernels.h"
 #include "lbm.h"
+#include "pair.h"
 
 using namespace lbm;
 
@@ -71,10 +72,8 @@ bool short_x_chunks(int nx, int ny) { return (long long)((nx + 255) / 256) * ny 
 // viscous-moment nodes) are the slowest loads under the bulk's traffic (1024 x 512 FP32, CBC-RELAX
 // outflow: 35.4 -> 31.3 us per step; 256^2 FP64 15.6 -> 15.4 us); D2Q9 takes 16 rows (256 x 128:
 // 7.7 -> 6.8 us per step).
-int chunk_rows_x(int M, int nx, int ny, bool cbc) {
-    if (!short_x_chunks(nx, ny)) return chunk_rows(M);
-    return M == 3 ? (cbc ? 8 : 12) : M == 2 ? 24 : 16;
-}
+int short_rows_x(int M, bool cbc) { return M == 3 ? (cbc ? 8 : 12) : M == 2 ? 24 : 16; }
+int chunk_rows_x(int M, int nx, int ny, bool cbc) { return short_x_chunks(nx, ny) ? short_rows_x(M, cbc) : chunk_rows(M); }
 // sides normal to y (coalesced pulls) take half-height chunks on the same small grids: their
 // reconstruction and corner chunks then end sooner
 int chunk_rows_y(int M, int nx, int ny) { return short_x_chunks(nx, ny) ? chunk_rows(M) / 2 : chunk_rows(M); }
@@ -88,15 +87,37 @@ int adj_rows_short(int M, int nx, int ny) {
     return M == 3 ? 12 : M == 2 ? 24 : 48;   // D2Q37: 16 -> 12 rows, 36.34 -> 36.07 us per 256^2 reverse step
 }
 
+// Two steps per pass: columns per thread group, output columns per tile, band width and x-band pitch,
+// work-groups that are resident at once, tiles per row and row segments; use: whether lbm_step takes
+// the pass for this grid.
+struct PairPlan {
+    int nt = 0, wo = 0, bw = 0, cpx = 0, wgs = 0, ntx = 0, nseg = 0;
+    bool use = false;
+};
+
 struct Layout {
     int Q = 0, M = 0, MS = 0;
     size_t esz = 0;
     unsigned long long pitch = 0;   // padded row length of a population plane (elements)
     size_t f_bytes = 0, region_bytes = 0, off_region = 0, off_inlet[4] = {0, 0, 0, 0}, off_diag = 0, total = 0;
     int diag_blocks = 0;
+    // two steps per pass (pair.h): tile shape, and where a grid has boundaries the state of the
+    // sides at the level between the two steps and the band buffers
+    PairPlan pair;
+    size_t off_mid = 0, off_cx = 0, off_cy = 0;
     SideDev s[4];
     CornerDev c[4];
 };
+
+template <int Q, typename T> constexpr PairPlan pair_shape() {
+    PairPlan p;
+    p.nt = pair_cols<Q, T>();
+    p.wo = (p.nt - 2 * Lat<Q>::M) * (int)sizeof(T) / 64 * 64 / (int)sizeof(T);
+    p.bw = BW<Q>;
+    p.cpx = CPX<Q>;
+    p.wgs = 256 * std::max(1, std::min(2048 / (2 * p.nt) / 2, (int)(160 * 1024 / ((size_t)ring_slots<Q>() * p.nt * sizeof(T)))));
+    return p;
+}
 
 int validate(const lbm_config* c, std::string& err) {
     if (!c) { err = "null config"; return LBM_E_ARG; }
@@ -131,6 +152,35 @@ int validate(const lbm_config* c, std::string& err) {
         for (int s = 0; s < 4; ++s)
             if (is_full(c->bc[s])) { err = "CBC with viscous terms needs a thermal stencil (D2Q17 or D2Q37)"; return LBM_E_UNSUPPORTED; }
     return LBM_OK;
+}
+
+// sides whose layers change with time: their level n + 1 goes through a band buffer
+bool band_side(int b) { return is_char(b) || b == BC_ZG; }
+
+// Whether lbm_step takes two steps per pass on this grid, and the pass's tiles.  A segment recomputes
+// 2 M rows and starts cold, so it needs some rows of its own: 3 M + 1, where the pass is still the
+// faster one (per step, periodic boxes: D2Q37 FP32 1024 x 512, 10 rows, 30.2 -> 28.4 us; FP64 700 x 500,
+// 11 rows, 39.5 -> 27.6 us; D2Q9 FP32 1023 x 700, 6 rows, 13.7 -> 8.2 us).  Boundaries cost two launches
+// per pass that nothing hides (about 20 us each for M = 3, 6 us for M = 1), which the saved traffic has
+// to pay for: the bytes of one single step from which it does (LODI-RELAX / CBC-RELAX sides, per step:
+// D2Q37 FP32 1500 x 1000 (444 MB) 79.5 -> 75.9 us, 1024 x 1024 (310 MB) 58.0 -> 62.1; FP64 1024 x 512
+// (310 MB) 58.7 -> 56.1, 700 x 500 (207 MB) 40.7 -> 42.6; D2Q17 FP32 2048 x 1024 (285 MB) equal; FP64
+// 1500 x 1000 (408 MB) 76.1 -> 60.2; D2Q9 FP32 1500 x 1000 (108 MB) 25.1 -> 21.8).
+PairPlan pair_plan(const lbm_config* c) {
+    const bool f64 = c->precision == LBM_FP64;
+    PairPlan p = c->stencil == 9 ? (f64 ? pair_shape<9, double>() : pair_shape<9, float>())
+               : c->stencil == 17 ? (f64 ? pair_shape<17, double>() : pair_shape<17, float>())
+                                  : (f64 ? pair_shape<37, double>() : pair_shape<37, float>());
+    const int M = stencil_M(c->stencil);
+    const bool xp = c->bc[0] == BC_PERIODIC, yp = c->bc[2] == BC_PERIODIC;
+    const int rows = yp ? c->ny : c->ny - 2 * M;
+    if (c->nx < 2 * p.bw || c->ny < 2 * p.bw || rows < 1) return p;
+    p.ntx = ((xp ? c->nx : c->nx - M) + p.wo - 1) / p.wo;
+    p.nseg = std::max(1, std::min(p.wgs / p.ntx, rows));
+    const double bytes = 2.0 * c->stencil * (f64 ? 8 : 4) * c->nx * c->ny;
+    const double least = xp && yp ? 0.0 : c->stencil == 9 ? 110e6 : c->stencil == 17 ? (f64 ? 240e6 : 330e6) : (f64 ? 300e6 : 440e6);
+    p.use = rows / p.nseg >= 3 * M + 1 && bytes >= least;
+    return p;
 }
 
 void make_layout(const lbm_config* c, Layout& L) {
@@ -211,6 +261,13 @@ void make_layout(const lbm_config* c, Layout& L) {
     L.diag_blocks = (int)(((unsigned long long)c->nx + 255) / 256 * c->ny);   // one per 256-node row tile
     L.off_diag = off;
     off += align_up((size_t)(L.diag_blocks + 1) * 8 * 8);
+    L.pair = pair_plan(c);
+    if (L.pair.use && !(xp && yp)) {
+        const bool xb = band_side(c->bc[0]) || band_side(c->bc[1]), yb = band_side(c->bc[2]) || band_side(c->bc[3]);
+        L.off_mid = off; off += L.region_bytes;
+        if (xb) { L.off_cx = off; off += align_up((size_t)L.Q * L.pair.cpx * c->ny * L.esz); }
+        if (yb) { L.off_cy = off; off += align_up((size_t)L.Q * L.pitch * 2 * L.pair.bw * L.esz); }
+    }
     L.total = off;
 }
 
@@ -258,6 +315,8 @@ struct lbm_ctx {
     int timing = 0;                // time every timing-th step launch (0: off)
     size_t tcalls = 0;             // step launches since timing was set
     std::vector<hipEvent_t> tev;   // pairs: start, end
+    std::vector<int> tsteps;       // per pair: steps of the timed launches that count (1; up to 2 of 2)
+    std::vector<int> tof;          // per pair: steps that the timed launches advance
     size_t tcount = 0;             // recorded pairs
     Tape tape;
     // the adjoint's second stream (non-blocking, default priority) and its events, made on the
@@ -316,10 +375,14 @@ BndArgs make_bnd(const lbm_ctx* c) {
 
 constexpr size_t MAX_TIMED = 65536;
 
-// launch the step kernel, bracketed by timing events when kernel timing is on
+// launch the step kernel (or a pass of nsteps = 2 steps), bracketed by timing events when kernel
+// timing is on: every timing-th step counts, with its share of the bracketed time
 template <typename F>
-hipError_t timed_launch(lbm_ctx* c, F&& launch) {
-    const bool rec = c->timing > 0 && (c->tcalls++ % (size_t)c->timing) == 0 && c->tcount < MAX_TIMED;
+hipError_t timed_launch(lbm_ctx* c, int nsteps, F&& launch) {
+    int count = 0;
+    if (c->timing > 0)
+        for (int k = 0; k < nsteps; ++k) count += (c->tcalls++ % (size_t)c->timing) == 0;
+    const bool rec = count > 0 && c->tcount < MAX_TIMED;
     if (rec) {
         while (c->tev.size() < 2 * (c->tcount + 1)) {
             hipEvent_t e;
@@ -336,6 +399,10 @@ hipError_t timed_launch(lbm_ctx* c, F&& launch) {
     if (rec) {
         r = hipEventRecord(c->tev[2 * c->tcount + 1], c->stream);
         if (r != hipSuccess) return r;
+        c->tsteps.resize(c->tcount);
+        c->tof.resize(c->tcount);
+        c->tsteps.push_back(count);
+        c->tof.push_back(nsteps);
         c->tcount += 1;
     }
     return hipSuccess;
@@ -367,9 +434,77 @@ int launch_step(lbm_ctx* c) {
     char* rc = c->region[c->cur];
     char* rn = c->region[c->cur ^ 1];
     auto step = [&](hipStream_t s) { launch_step_raw<Q, T, false>(c, A, B, rc, rn, nullptr, s); };
-    HIPCHK(c, timed_launch(c, step));
+    HIPCHK(c, timed_launch(c, 1, step));
     c->cur ^= 1;
     c->steps += 1;
+    return LBM_OK;
+}
+
+// two steps in one pass over HBM (pair.h): the sides to n + 1 (into the band buffers, with the bulk
+// nodes next to them), the sides to n + 2, the bulk to n + 2
+template <int Q, typename T>
+int launch_pair(lbm_ctx* c) {
+    const Layout& L = c->L;
+    const PairPlan& pp = L.pair;
+    const T* A = (const T*)c->f[c->cur];
+    T* B = (T*)c->f[c->cur ^ 1];
+    const lbm_config& cfg = c->cfg;
+    const bool px = cfg.bc[0] == BC_PERIODIC, py = cfg.bc[2] == BC_PERIODIC;
+    PairArgs<T> g;
+    std::memset(&g, 0, sizeof(g));
+    const BulkArgs& k = c->bulk;
+    g.nx = k.nx; g.ny = k.ny; g.x0 = k.x0; g.x1 = k.x1; g.y0 = k.y0; g.y1 = k.y1;
+    g.pitch = k.pitch; g.omega_f = k.omega_f; g.omega_d = k.omega_d;
+    g.wo = pp.wo; g.ntx = pp.ntx; g.nseg = pp.nseg;
+    T* cx = L.off_cx ? (T*)(c->ws + L.off_cx) : nullptr;
+    T* cy = L.off_cy ? (T*)(c->ws + L.off_cy) : nullptr;
+    const View<T> band[4] = {{cx, (unsigned long long)pp.cpx}, {cx + pp.cpx - k.nx, (unsigned long long)pp.cpx},
+                             {cy, k.pitch}, {cy + (long long)(2 * pp.bw - k.ny) * Q * (long long)k.pitch, k.pitch}};
+    BandArgs<T> to, from;
+    std::memset(&to, 0, sizeof(to));
+    std::memset(&from, 0, sizeof(from));
+    for (int s = 0; s < 4; ++s) {
+        to.src[s] = {A, k.pitch};
+        const bool b = band_side(cfg.bc[s]);
+        from.src[s] = b ? band[s] : to.src[s];
+        g.lay[s] = from.src[s];   // a Dirichlet side's layers are the same at every level
+        (s < 2 ? to.xb[s] : to.yb[s - 2]) = b;
+    }
+    to.nbx = (k.y1 - k.y0 + 1 + 15) / 16;
+    to.nby = (pp.bw - L.M) * ((k.x1 + 256) / 256);
+    const int nband = to.nbx * (to.xb[0] + to.xb[1]) + to.nby * (to.yb[0] + to.yb[1]);
+    auto pass = [&](hipStream_t s) {
+        if (nband > 0) {
+            BndArgs a = make_bnd(c);
+            // nothing hides these launches: short chunks whatever the grid (see chunk_rows_x)
+            int nbnd = 0;
+            for (int k = 0; k < 4; ++k) {
+                SideDev& d = a.s[k];
+                if (d.kind == KIND_CHAR) {
+                    d.rows = d.nax == 0 ? short_rows_x(L.M, is_full(cfg.bc[k])) : chunk_rows(L.M) / 2;
+                    d.nblk = (d.len + d.rows - 1) / d.rows;
+                }
+                d.blk0 = nbnd;
+                nbnd += d.nblk;
+            }
+            char* end = a.reg_next;
+            a.reg_next = c->ws + L.off_mid;
+            const BandDst<T> dst = {cx, cy, k.pitch, k.nx, k.ny, pp.bw, pp.cpx};
+            hipLaunchKernelGGL((k_bnd<Q, T, true, BandDst<T>>), dim3(nbnd + nband), dim3(256), 0, s, to, dst, a, k, nbnd);
+            a.reg_cur = a.reg_next;
+            a.reg_next = end;
+            const GridDst<T> out = {B, k.pitch};
+            hipLaunchKernelGGL((k_bnd<Q, T, false, GridDst<T>>), dim3(nbnd), dim3(256), 0, s, from, out, a, k, nbnd);
+        }
+        const dim3 grid(pp.ntx * pp.nseg), block(2 * pp.nt);
+        if (px && py) hipLaunchKernelGGL((k_pair<Q, T, true, true>), grid, block, 0, s, A, B, g);
+        else if (px) hipLaunchKernelGGL((k_pair<Q, T, true, false>), grid, block, 0, s, A, B, g);
+        else if (py) hipLaunchKernelGGL((k_pair<Q, T, false, true>), grid, block, 0, s, A, B, g);
+        else hipLaunchKernelGGL((k_pair<Q, T, false, false>), grid, block, 0, s, A, B, g);
+    };
+    HIPCHK(c, timed_launch(c, 2, pass));
+    c->cur ^= 1;
+    c->steps += 2;
     return LBM_OK;
 }
 
@@ -807,9 +942,12 @@ int lbm_dirichlet_profile(lbm_ctx* c, int side, const double* d_U) {
 int lbm_step(lbm_ctx* c, int nsteps) {
     if (!c) return fail(nullptr, LBM_E_ARG, "null context");
     if (nsteps < 0) return fail(c, LBM_E_ARG, "nsteps < 0");
-    for (int k = 0; k < nsteps; ++k) {
-        const int rc = dispatch(c, [&]<int Q, typename T>() -> int { return launch_step<Q, T>(c); });
+    for (int k = 0; k < nsteps;) {
+        // two steps at once, unless a check falls between them
+        const bool two = c->L.pair.use && k + 1 < nsteps && !(c->diag_every > 0 && (c->steps + 1) % c->diag_every == 0);
+        const int rc = dispatch(c, [&]<int Q, typename T>() -> int { return two ? launch_pair<Q, T>(c) : launch_step<Q, T>(c); });
         if (rc != LBM_OK) return rc;
+        k += two ? 2 : 1;
         if (c->diag_every > 0 && c->steps % c->diag_every == 0) {
             double out[8];
             const int rd = host_diag(c, out);
@@ -988,14 +1126,16 @@ int lbm_bulk_kernel_time(lbm_ctx* c, double* total_ms, long* launches) {
     if (!c) return fail(nullptr, LBM_E_ARG, "null context");
     if (!total_ms || !launches) return fail(c, LBM_E_ARG, "output pointer is NULL");
     double sum = 0.0;
+    long n = 0;
     for (size_t k = 0; k < c->tcount; ++k) {
         HIPCHK(c, hipEventSynchronize(c->tev[2 * k + 1]));
         float ms = 0.0f;
         HIPCHK(c, hipEventElapsedTime(&ms, c->tev[2 * k], c->tev[2 * k + 1]));
-        sum += ms;
+        sum += (double)ms * c->tsteps[k] / c->tof[k];
+        n += c->tsteps[k];
     }
     *total_ms = sum;
-    *launches = (long)c->tcount;
+    *launches = n;
     return LBM_OK;
 }
 
