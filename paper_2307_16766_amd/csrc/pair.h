@@ -24,11 +24,11 @@
 // the boundary solve (x_f - M - 2 - M is the innermost node it reads).  Layers of Dirichlet sides
 // are the same at every level and are read from A itself.
 // What bounds it: in FP64 HBM (4.5-4.8 TB/s of useful traffic; the same loads and stores without the
-// collisions take 85 % of the time), in FP32 D2Q37 the vector ALU (about 790 instructions per node
+// collisions take 85 % of the time), in FP32 D2Q37 the vector ALU (about 680 instructions per node
 // and step: the pass without its loads and stores takes 60 % of the time).  Halo columns and rows
 // cost little traffic: HBM reads 1.06x, writes 1.01x of one single step's (counters, D2Q37 FP64
 // 4096 x 2048).  Measured per step against the single-step kernel: D2Q37 4096 x 2048 FP64 periodic
-// 820 -> 570 us, FP32 with Dirichlet / LODI-RELAX sides 417 -> 300 us; D2Q17 FP64 1950 x 1950 186 ->
+// 820 -> 570 us, FP32 with Dirichlet / LODI-RELAX sides 417 -> 295 us; D2Q17 FP64 1950 x 1950 186 ->
 // 108 us; D2Q9 FP32 2048 x 2048 58 -> 26 us.  Requesting rows two or three ahead changed nothing (the
 // loads are not the bound), tiles of half the columns with two work-groups per CU are slower (more
 // halo), unaligned output tiles too (partial lines).
@@ -184,6 +184,9 @@ __global__ __launch_bounds__((2 * pair_cols<Q, T>()), 1) void k_pair(const T* A,
     const int t = (int)threadIdx.x - group * NT;
     const T omega = sizeof(T) == 4 ? (T)g.omega_f : (T)g.omega_d;
     if (group == 0) {
+        // the row hangs on this group's chain (loads, collision, hand-over): it issues first (the pass
+        // alone 2 % faster on D2Q37 FP32, 4 % on D2Q17 FP32)
+        __builtin_amdgcn_s_setprio(2);
         // tiles that hold layer columns take the loads with per-lane addresses
         if (!PX && (X0 - M < g.x0 || X0 - M + NT - 1 > g.x1)) pair_producer<Q, T, NT, PX, PY, true>(A, g, X0, Y0, Y1, t, omega, ring);
         else pair_producer<Q, T, NT, PX, PY, false>(A, g, X0, Y0, Y1, t, omega, ring);
