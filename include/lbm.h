@@ -237,7 +237,8 @@ int lbm_bulk_kernel_time(lbm_ctx* ctx, double* total_ms, long* launches);
  * lbm_record: from the initial state (no step taken since lbm_init; else LBM_E_STATE), advance
  * nsteps steps exactly as lbm_step does while storing the checkpoints in d_tape (caller-owned,
  * 256-byte aligned, at least lbm_tape_bytes bytes, borrowed until the next lbm_record, the
- * context's destruction, or lbm_restore, which discards the recording).
+ * context's destruction, or lbm_restore, which discards the recording).  The steps of the last two
+ * segments also fill the two recomputation sets.
  *
  * lbm_adjoint: gradient of a scalar loss L of the final macroscopic fields with respect to the
  * initial fields and the relaxation parameters.  d_seed: device FP64 [4][ny][nx] =
@@ -247,7 +248,8 @@ int lbm_bulk_kernel_time(lbm_ctx* ctx, double* total_ms, long* launches);
  * dL/d(rho0, u_x0, u_y0, T0) of the fields given to lbm_init; h_grad_relax (host [4][2])
  * receives dL/dsigma and dL/dalpha of each side (0 for sides without relaxation).  Runs the
  * reverse sweep segment by segment from the last checkpoint: each segment is recomputed from
- * its checkpoint, then reversed step by step.  The recomputation runs on a second stream that
+ * its checkpoint, unless the first call after lbm_record finds it in its set, then reversed step
+ * by step.  The recomputation runs on a second stream that
  * the library makes on the context's first lbm_adjoint (non-blocking, default priority, on the
  * device current at that call, which must be the context's; released by lbm_destroy), one
  * segment ahead of the reverse sweep on the context's stream; events order the two.  The

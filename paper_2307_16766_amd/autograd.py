@@ -21,8 +21,10 @@ class ThermalLBMFunction(torch.autograd.Function):
                       (rho0.detach(), ux0.detach(), uy0.detach(), T0.detach()), precision=spec.get("precision", "fp64"))
         relax = dict(spec.get("relax", {}))
         relax_sides = [s for s, b in enumerate(spec["bc"]) if b in ("lodi_relax", "cbc_relax")]
+        if relax_sides:
+            sg, al = float(sigma), float(alpha)   # each reads the device: once, not per side
         for s in relax_sides:
-            sim.set_relax(s, sigma=float(sigma), alpha=float(alpha), **relax)
+            sim.set_relax(s, sigma=sg, alpha=al, **relax)
         if spec.get("visc"):
             sim.set_viscous(-1, spec["visc"])
         sim.record(spec["nsteps"], spec.get("every", 50))
@@ -40,8 +42,9 @@ class ThermalLBMFunction(torch.autograd.Function):
         dev = grad.device
         sim.close()
         ctx.sim = None
-        return (torch.tensor(float(dsig), dtype=torch.float64, device=dev),
-                torch.tensor(float(dalp), dtype=torch.float64, device=dev),
+        # filled on the device: a copy from host memory would wait for it
+        return (torch.full((), float(dsig), dtype=torch.float64, device=dev),
+                torch.full((), float(dalp), dtype=torch.float64, device=dev),
                 grad[0], grad[1], grad[2], grad[3], None)
 
 

@@ -622,6 +622,10 @@ __device__ void corner_rk4(const BndArgs& a, const CornerDev& c, bool owner, con
     for (int m = 0; m < 4; ++m) acc[m] = Un[m];
     const double ln[4] = {Un[0], Un[1] * c.ndx + Un[2] * c.ndy, -Un[1] * c.ndy + Un[2] * c.ndx, Un[3]};
     const double s0 = char_speed<Q>(ln);
+    // the same code with and without HIST, to the compiler too: which products it fuses with the sums
+    // they enter depends on the basic blocks, and a recorded run rounds as a plain one does
+    int hist = HIST;
+    asm("" : "+s"(hist));
     for (int st = 0; st < 4; ++st) {
         const double th = ast[st];
         double Y[4], B1[4], B2[4];
@@ -630,10 +634,10 @@ __device__ void corner_rk4(const BndArgs& a, const CornerDev& c, bool owner, con
             B1[m] = (1.0 - th) * D1n[m] + th * D1p[m];
             B2[m] = (1.0 - th) * D2n[m] + th * D2p[m];
         }
-        if (HIST && owner && st > 0)
-            for (int m = 0; m < 4; ++m) ((double*)(a.reg_next + c.off_cs))[(st - 1) * 4 + m] = Y[m];
         corner_rate<Q>(c, Y, B1, B2, ln, s0, k4);
         for (int m = 0; m < 4; ++m) acc[m] += bst[st] * (1.0 / 6.0) * k4[m];
+        if (hist && owner && st > 0)
+            for (int m = 0; m < 4; ++m) ((double*)(a.reg_next + c.off_cs))[(st - 1) * 4 + m] = Y[m];
     }
     for (int m = 0; m < 4; ++m) cp_out[m] = acc[m];
     if (owner) {
