@@ -17,8 +17,8 @@
 //   adjoint region (same offsets as the forward region): direct adjoints of U_b^n, of the
 //          strip X^n and corner diagonal D^n as time-n inputs, and of U_c^n.
 // One reverse step n+1 -> n is two launches (three when the corners read the sides' terms):
-//   k_adj_side   : per chunk of side rows, fold lambda^{n+1} of the layers into the adjoint of
-//                  U_b^{n+1} (J_feq^T), reverse the four RK4 stages (stage inputs stored by the
+//   k_adj_side   : per chunk of side rows, from the adjoint of U_b^{n+1} (which has the fold of
+//                  lambda^{n+1} of the layers, J_feq^T), reverse the four RK4 stages (stage inputs stored by the
 //                  recomputation) with a hand-written VJP of the characteristic rate, emit the
 //                  adjoints of U_b^n and X^n, add the adjoint of X^{n+1} to nu^{n+1}(x_f) through
 //                  J_m^T, and accumulate the adjoints of K and alpha; further blocks reverse the
@@ -28,7 +28,7 @@
 //                  the corner diagonal nodes' corrections), nu^n = J_C^T lambda^n at bulk nodes:
 //                  nu_i = (1 - omega) lambda_i + omega (G_0 + c_ix G_1 + c_iy G_2 + |c_i|^2 G_3),
 //                  G = (dm/dM)^T (df^eq/dm)^T lambda, M the linear moments (sum f, sum f c,
-//                  sum f |c|^2); at n = 0 it gives dL/d(rho0, ux0, uy0, T0) = (df^eq/dm)^T lambda^0.
+//                  sum f |c|^2); lambda^n of the layers is folded into the adjoint of U_b^n; at n = 0 it gives dL/d(rho0, ux0, uy0, T0) = (df^eq/dm)^T lambda^0.
 // Supported boundaries: all of them.  CBC sides with the mesoscopic viscous terms add their VJP
 // at the nodes x_f - M .. x_f - M - 2, NEEP and zero-gradient sides add terms of nu^{n+1}(x_f); the layers
 // of a Dirichlet side are constants of the given profile, or, with the default profile (the
@@ -469,7 +469,6 @@ __device__ void adj_chunk(const AdjArgs& g, const SideDev& sd, int side, int blk
     const int r1 = min(r0 + g.arows[side], len);
     const int nlr = min(NR, r1 - r0 + 2 * H);   // LDS rows in use
     const double* ubn = (const double*)(a.reg_cur + sd.off_ub);
-    const double* ubp = (const double*)(a.reg_next + sd.off_ub);
     const double* stn = (const double*)(a.reg_cur + sd.off_strip);
     const double* stp = (const double*)(a.reg_next + sd.off_strip);
     const double* mub1 = (const double*)(g.adj_next + sd.off_ub);
@@ -489,7 +488,7 @@ __device__ void adj_chunk(const AdjArgs& g, const SideDev& sd, int side, int blk
     // overlap (a store to LDS waits for its value, and waits on loads go in issue order)
     const bool fold = node && within(r, 4);
     const int rp = node ? phys(r) : 0;
-    double y0v[4], yv[3][4], u4[4], mb[4], lam[Q];
+    double y0v[4], yv[3][4];
     if (node) {
         // stage inputs Y_0 = U_b^n and Y_1..Y_3 (stored by the recomputation of this step)
         const double* ys = (const double*)(a.reg_next + sd.off_stage);
@@ -497,12 +496,21 @@ __device__ void adj_chunk(const AdjArgs& g, const SideDev& sd, int side, int blk
         for (int st = 1; st <= 3; ++st)
             for (int m = 0; m < 4; ++m) yv[st - 1][m] = ys[(((size_t)(st - 1) * M + jj) * len + rp) * 4 + m];
     }
-    if (fold) {   // lambda^{n+1} of this layer node, folded into the adjoint of U_b^{n+1} below
-        for (int m = 0; m < 4; ++m) u4[m] = ubp[((size_t)jj * len + rp) * 4 + m];
-        for (int m = 0; m < 4; ++m) mb[m] = mub1[((size_t)jj * len + rp) * 4 + m];
-        int x, y; side_node(sd, j, rp, x, y);
+    if (fold)   // lambda^{n+1} of the layers is in it already (k_adj_bulk, k_adj_seed)
+        for (int m = 0; m < 4; ++m) yb1[m] = mub1[((size_t)jj * len + rp) * 4 + m];
+    // nu^{n+1} of the strip nodes, changed at the end, is requested here too: in D2Q17 and D2Q37 a
+    // thread owns at most one
+    constexpr bool PRE = NR * MS <= 256;
+    double nux[PRE ? Q : 1];
+    auto strip_owned = [&](int e) { const int rr = r0 - H + e / MS; return e < NR * MS && rr >= r0 && rr < r1 && valid(rr); };
+    auto strip_nu = [&](int e) {
+        int x, y; side_node(sd, -(e % MS), phys(r0 - H + e / MS), x, y);
+        return g.V1 + pix<Q>(a.pitch, 0, x, y);
+    };
+    if constexpr (PRE) if (strip_owned(tid)) {
+        const double* v1 = strip_nu(tid);
 #pragma unroll
-        for (int i = 0; i < Q; ++i) lam[i] = g.V1[pix<Q>(a.pitch, i, x, y)];
+        for (int i = 0; i < Q; ++i) nux[i] = v1[(unsigned long long)i * a.pitch];
     }
     double cval = 0.0;
     // this work-group's running sums of the parameter adjoints, added to at the end
@@ -531,11 +539,6 @@ __device__ void adj_chunk(const AdjArgs& g, const SideDev& sd, int side, int blk
         for (int m = 0; m < 4; ++m) sY[0][t * 4 + m] = y0v[m];
         for (int st = 1; st <= 3; ++st)
             for (int m = 0; m < 4; ++m) sY[st][t * 4 + m] = yv[st - 1][m];
-    }
-    if (fold) {
-        double G[4];
-        feq_vjp<Q>(u4, lam, G);
-        for (int m = 0; m < 4; ++m) yb1[m] = mb[m] + G[m];
     }
     if (tid < 2 * 2 * M * 4) (&sCb[0][0][0][0])[tid] = 0.0;
     // mesoscopic viscous terms of time n (CBC sides without -FD), as in the forward step
@@ -833,17 +836,18 @@ __device__ void adj_chunk(const AdjArgs& g, const SideDev& sd, int side, int blk
     // nu^{n+1}(x_f) as phi . (dm/dM)^T Xbar, except at the end rows next to corners (the corner
     // diagonal node c + v, shared with the other side and the corner), whose term goes to gm
     for (int e = tid; e < NR * MS; e += blockDim.x) {
-        const int l2 = e / MS, k = e % MS, rr = r0 - H + l2;
-        if (rr < r0 || rr >= r1 || !valid(rr)) continue;
-        const int rp = phys(rr);
+        if (!strip_owned(e)) continue;
+        const int k = e % MS, rp = phys(r0 - H + e / MS);
         const size_t o = ((size_t)k * len + rp) * 4;
         const bool end_row = !tper && k == 0 && (rp == 0 || rp == len - 1);   // len >= 3: the two ends differ
-        int x, y; side_node(sd, -k, rp, x, y);
-        double* v1 = g.V1 + pix<Q>(a.pitch, 0, x, y);
+        double* v1 = strip_nu(e);
         // every load before the first store (one round trip)
         double Z[4], v[Q];
         for (int m = 0; m < 4; ++m) Z[m] = xbp[o + m];
-        if (!end_row) {
+        if constexpr (PRE) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) v[i] = nux[i];
+        } else if (!end_row) {
 #pragma unroll
             for (int i = 0; i < Q; ++i) v[i] = v1[(unsigned long long)i * a.pitch];
         }
@@ -1125,6 +1129,20 @@ __global__ __launch_bounds__(256) void k_adj_dir_collect(AdjArgs g, int s, int n
     }
 }
 
+// byte offset of layer node (x, y) of a characteristic side in the U_b part of a region, or -1
+template <int Q>
+__device__ __forceinline__ long long layer_slot(const BndArgs& a, int x, int y) {
+    long long u = -1;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const SideDev& S = a.s[s];
+        if (S.kind != KIND_CHAR) continue;
+        const int j = ((S.nax == 0 ? x : y) - S.xf) * S.sn, r = (S.nax == 0 ? y : x) - S.r0;
+        if (j >= 1 && j <= Lat<Q>::M && r >= 0 && r < S.len) u = (long long)S.off_ub + ((long long)(j - 1) * S.len + r) * 32;
+    }
+    return u;
+}
+
 // ------------------------------------------------------------------ bulk reverse
 // One thread per node (all nodes; 256-node tiles of one row).  INIT: the reverse of the
 // initialisation f^0 = f^eq(fields) at every node; the fields are read back as the moments of
@@ -1134,9 +1152,24 @@ __global__ __launch_bounds__(256) void k_adj_bulk(AdjArgs g, BulkArgs k, int bpr
     const int x = (blockIdx.x % bpr) * 256 + threadIdx.x, y = blockIdx.x / bpr;
     if (x >= k.nx) return;
     const unsigned long long pitch = k.pitch;
-    // this node's moments of time n, loaded with the pull (every node has them)
+    // this node's moments of time n, loaded with the pull: of bulk nodes (and at time 0) from mom, of a
+    // layer node of a characteristic side its U_b
     const unsigned long long plane = (unsigned long long)k.ny * pitch, o = (unsigned long long)y * pitch + x;
-    const double m[4] = {g.mom[o], g.mom[plane + o], g.mom[2 * plane + o], Lat<Q>::thermal ? g.mom[3 * plane + o] : 1.0};
+    const bool bulk = x >= k.x0 && x <= k.x1 && y >= k.y0 && y <= k.y1;
+    const double* mp = g.mom + o;
+    unsigned long long mstep = plane;
+    double* mub = nullptr;   // the adjoint of that U_b, written by this step's side chunks
+    double mb[4] = {0.0, 0.0, 0.0, 0.0};
+    if (!INIT && !bulk) {
+        const long long u = layer_slot<Q>(g.b, x, y);
+        if (u >= 0) {
+            mp = (const double*)(g.b.reg_cur + u);
+            mstep = 1;
+            mub = (double*)(g.adj_cur + u);
+            for (int c = 0; c < 4; ++c) mb[c] = mub[c];
+        }
+    }
+    const double m[4] = {mp[0], mp[mstep], mp[2 * mstep], Lat<Q>::thermal ? mp[3 * mstep] : 1.0};
     double lam[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
@@ -1236,11 +1269,18 @@ __global__ __launch_bounds__(256) void k_adj_bulk(AdjArgs g, BulkArgs k, int bpr
         for (int a = 0; a < 4; ++a) g.grad[a * n + id] = G[a];
         return;
     }
-    const bool bulk = x >= k.x0 && x <= k.x1 && y >= k.y0 && y <= k.y1;
     double* out = g.V0 + pix<Q>(pitch, 0, x, y);
+    double G[4], GM[4];
+    feq_vjp<Q>(m, lam, G);
     if (!bulk) {
 #pragma unroll
         for (int i = 0; i < Q; ++i) out[(unsigned long long)i * pitch] = lam[i];
+        // a layer holds f^eq(U_b): the fold of its lambda into the adjoint of U_b, here, where the
+        // bulk nodes take the same derivative and every node is a thread, not in the side chunks,
+        // whose few work-groups the step waits for: they took 16.6 us of 37 loads a thread and this
+        // derivative on 256 x 256 (D2Q37, LODI-RELAX sides), now 14.3; this kernel is as long as before
+        if (mub)
+            for (int c = 0; c < 4; ++c) mub[c] = mb[c] + G[c];
         if (g.dir_any) {
             // lambda^{n+1} of a default-profile layer node goes to its row's profile (lambda^n is
             // taken by the next reverse step, lambda^0 by the INIT pass)
@@ -1254,8 +1294,6 @@ __global__ __launch_bounds__(256) void k_adj_bulk(AdjArgs g, BulkArgs k, int bpr
         }
         return;
     }
-    double G[4], GM[4];
-    feq_vjp<Q>(m, lam, G);
     mom_vjp<Q>(m, G, GM);
     const double om = k.omega_d;
 #pragma unroll
@@ -1299,10 +1337,11 @@ __global__ __launch_bounds__(256) void k_adj_bulk(AdjArgs g, BulkArgs k, int bpr
 // ------------------------------------------------------------------ seed at the final step
 // V^N = J_m^T dL/dm at every node (nu at bulk nodes, lambda at layer and block nodes).  seed:
 // dL/d(rho, ux, uy, T) [4][ny][nx], or NULL for the pressure loss sum over the bulk nodes of
-// (P - cs^2)^2, P = cs^2 rho T.
+// (P - cs^2)^2, P = cs^2 rho T.  Of layer nodes lambda^N is folded into the adjoint of U_b^N (adj_cur;
+// reg_cur: the region of time N), as k_adj_bulk does at earlier times.
 template <int Q, typename T>
 __global__ __launch_bounds__(256) void k_adj_seed(const T* __restrict__ F, const double* __restrict__ seed, double* V,
-                                                  BulkArgs k, int bpr) {
+                                                  AdjArgs g, BulkArgs k, int bpr) {
     const int x = (blockIdx.x % bpr) * 256 + threadIdx.x, y = blockIdx.x / bpr;
     if (x >= k.nx) return;
     double d[Q];
@@ -1323,8 +1362,18 @@ __global__ __launch_bounds__(256) void k_adj_seed(const T* __restrict__ F, const
     }
     double GM[4];
     mom_vjp<Q>(m, s, GM);
+    double lam[Q];
 #pragma unroll
-    for (int i = 0; i < Q; ++i) V[pix<Q>(k.pitch, i, x, y)] = phi_dot<Q>(i, GM);
+    for (int i = 0; i < Q; ++i) V[pix<Q>(k.pitch, i, x, y)] = lam[i] = phi_dot<Q>(i, GM);
+    if (x >= k.x0 && x <= k.x1 && y >= k.y0 && y <= k.y1) return;
+    const long long slot = layer_slot<Q>(g.b, x, y);
+    if (slot < 0) return;
+    const double* ub = (const double*)(g.b.reg_cur + slot);
+    const double ubm[4] = {ub[0], ub[1], ub[2], Lat<Q>::thermal ? ub[3] : 1.0};
+    double G[4];
+    feq_vjp<Q>(ubm, lam, G);
+    double* mub = (double*)(g.adj_cur + slot);
+    for (int c = 0; c < 4; ++c) mub[c] = G[c];
 }
 
 // moments of a population buffer into (rho, ux, uy, T) planes (start of a recomputed segment)
@@ -1346,7 +1395,7 @@ __global__ __launch_bounds__(256) void k_adj_moments(const T* __restrict__ F, do
 // one source at a time (sides in order, then corners), so nodes shared by two sources are
 // updated in a fixed order.
 template <int Q>
-__global__ __launch_bounds__(256) void k_adj_final(AdjArgs g) {
+__global__ __launch_bounds__(1024) void k_adj_final(AdjArgs g) {
     constexpr int M = Lat<Q>::M, MS = (M == 1) ? 2 : 1;
     const BndArgs& a = g.b;
     const size_t n = (size_t)a.nx * a.ny;

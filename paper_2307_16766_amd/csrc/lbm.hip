@@ -605,8 +605,6 @@ int run_adjoint(lbm_ctx* c, const double* seed, double* grad, double* h_relax) {
     }
     hipStream_t ax = c->aux;
 
-    hipLaunchKernelGGL((k_adj_seed<Q, T>), dim3(bpr * ny), dim3(256), 0, st, (const T*)c->f[c->cur], seed, V[t.N & 1], bk, bpr);
-    HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipMemsetAsync(base + t.off_adj[0], 0, t.end_clear - t.off_adj[0], st));
 
     AdjArgs g;
@@ -662,6 +660,10 @@ int run_adjoint(lbm_ctx* c, const double* seed, double* grad, double* h_relax) {
         g.dacc[s] = (double*)(base + t.off_dacc[s]);
         g.dir_any = 1;
     }
+    g.b.reg_cur = c->region[c->cur];
+    g.adj_cur = base + t.off_adj[t.N & 1];
+    hipLaunchKernelGGL((k_adj_seed<Q, T>), dim3(bpr * ny), dim3(256), 0, st, (const T*)c->f[c->cur], seed, V[t.N & 1], g, bk, bpr);
+    HIPCHK(c, hipGetLastError());
     const int nside_blocks = t.nadj + ((any_corner && !g.coupled) ? 4 : 0);
 
     // Segment seg is recomputed from its checkpoint on the second stream into recomputation set
@@ -749,7 +751,7 @@ int run_adjoint(lbm_ctx* c, const double* seed, double* grad, double* h_relax) {
         HIPCHK(c, hipGetLastError());
     }
     g.adj_cur = base + t.off_adj[0];
-    hipLaunchKernelGGL((k_adj_final<Q>), dim3(1), dim3(256), 0, st, g);
+    hipLaunchKernelGGL((k_adj_final<Q>), dim3(1), dim3(1024), 0, st, g);
     HIPCHK(c, hipGetLastError());
     std::vector<double> acc((size_t)2 * t.nadj + 4);
     HIPCHK(c, hipMemcpyAsync(acc.data(), base + t.off_acc, acc.size() * 8, hipMemcpyDeviceToHost, st));
