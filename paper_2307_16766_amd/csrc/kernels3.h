@@ -9,14 +9,12 @@
 //
 // One time step = face kernels, which need only the old level A: k3_prep (strip and viscous
 // moments of the new level from pulls of A -- in FP64, read from the compact face strips that the
-// previous bulk launch wrote, see StripMap3 --, viscous terms of the old level), four k3_stage
-// launches (one per RK4 stage of the coupled face system) and k3_final (new layer populations:
-// equilibrium, eq. NEEP or zero gradient, staged in a small buffer); then the bulk kernel (fused
+// previous bulk launch wrote, see StripMap3 --, viscous terms of the old level); k3_rk4 (the four
+// stages of the coupled face system and the equilibrium of its result as the new layer populations,
+// staged in a small buffer) or, on large faces, four k3_stage launches (one per stage); k3_final (the
+// layer populations that k3_rk4 has not written: large faces, NEEP, zero gradient); then the bulk kernel (fused
 // pull-stream + moments + BGK, HBM-bound), whose boundary-layer lanes store the staged layer
-// populations with the bulk's own whole-line stores.  Separate launches replace the
-// halo recomputation of the two-dimensional boundary chunks: a face couples its rows in y and z,
-// so a chunk's halo would grow in two directions, while the face work is a small fraction of a
-// 3D step.
+// populations with the bulk's own whole-line stores.
 #pragma once
 
 #include "lattice3.h"
@@ -38,7 +36,7 @@ struct Args3 {
     double omega, tau;
     char* reg_cur;
     char* reg_next;
-    double* Ya;   // RK4 stage inputs [2][M][rows][5]
+    double* Ya;   // RK4 stage inputs [2][M][rows][5] (k3_stage)
     double* Yb;
     double* V;    // viscous terms of the old level [2][rows][5]
     Face3 f[2];
@@ -409,16 +407,20 @@ __global__ __launch_bounds__(256) void k3_prep(const T* __restrict__ A, const T*
 // dU/dt in the face frame (rho, u_n, u_t1, u_t2, T) of one layer node (Appendix A): amplitudes
 // L = Lambda S dU/dn, incoming ones by scheme (Tab. CBCs; relaxation on the incoming acoustic
 // wave with the acoustic rows' pressure coefficient 1/(5 rho cs^2)), then -S^-1 Lbar (+ T + V
-// for the CBC schemes).  yp/ym, zp/zm: the node's neighbours in y and z (same layer); U0: the
-// node at time t, which fixes the wave directions.
+// for the CBC schemes).  yp/ym, zp/zm: the node's neighbours in y and z (same layer); u0, s0: u_n and
+// the speed of sound at time t, which fix the wave directions.  One division and one square root: 1/rho
+// and 1/T~ from 1/(rho T~), every speed from sqrt(T~).
 __device__ __forceinline__ void char_rate3(const double* U, const double* dn, const double* yp, const double* ym,
-                                           const double* zp, const double* zm, const double* V, const double* U0,
+                                           const double* zp, const double* zm, const double* V, double u0, double s0,
                                            int scheme, double K, double alpha, double Pinf, double* rate) {
     constexpr double cs2 = L3::cs2;
     const bool full = is_full3(scheme);
     const bool relax = scheme == F3_LODI_RELAX || scheme == F3_CBC_RELAX;
     const double rho = U[0], un = U[1], v = U[2], w = U[3], T = U[4];
-    const double ir = 1.0 / rho;
+    const double irT = 1.0 / (rho * T), ir = irT * T, iT = irT * rho, sT = sqrt(T);
+    // sqrt(1 / (15 cs^2)), sqrt(gamma cs^2), sqrt(15 cs^2 / 4)
+    constexpr double r15c = 0.31622776601683794, sc = 1.0540925533894598, q15c = 1.5811388300841898;
+    static_assert(cs2 == 2.0 / 3.0);
     auto h = [](double a, double b) { return 0.5 * (a - b); };
     // transverse terms (Appendix A), central differences in y and z
     double Tt[5];
@@ -428,7 +430,7 @@ __device__ __forceinline__ void char_rate3(const double* U, const double* dn, co
     Tt[3] = -cs2 * ir * h(zp[0] * zp[4], zm[0] * zm[4]) - (v * h(yp[3], ym[3]) + w * h(zp[3], zm[3]));
     Tt[4] = -(T * (1.0 / CV)) * (h(yp[2], ym[2]) + h(zp[3], zm[3])) - (v * h(yp[4], ym[4]) + w * h(zp[4], zm[4]));
     const double er = T * ir;                          // T~ / (rho cs^2)
-    const double r15 = sqrt(T * (1.0 / (15.0 * cs2)));
+    const double r15 = r15c * sT;
     auto Sx = [&](const double* x, double* o) {
         o[0] = -0.4 * er * x[0] + 0.6 * x[4];
         o[1] = x[2];
@@ -436,7 +438,7 @@ __device__ __forceinline__ void char_rate3(const double* U, const double* dn, co
         o[3] = 0.2 * er * x[0] - r15 * x[1] + 0.2 * x[4];
         o[4] = 0.2 * er * x[0] + r15 * x[1] + 0.2 * x[4];
     };
-    const double s = sqrt(GAMMA * cs2 * T), s0 = sqrt(GAMMA * cs2 * U0[4]), u0 = U0[1];
+    const double s = sc * sT;
     double Sd[5], ST[5];
     Sx(dn, Sd);
     Sx(Tt, ST);
@@ -456,7 +458,7 @@ __device__ __forceinline__ void char_rate3(const double* U, const double* dn, co
     }
     double Bv[5];
     for (int m = 0; m < 5; ++m) Bv[m] = lam0[m] >= 0.0 ? lam[m] * Sd[m] : in[m];
-    const double rT = rho / T, q15 = sqrt(15.0 * cs2 / (4.0 * T));
+    const double rT = rho * iT, q15 = q15c * sT * iT;
     rate[0] = rT * Bv[0] - 1.5 * rT * (Bv[3] + Bv[4]);
     rate[1] = q15 * (Bv[3] - Bv[4]);
     rate[2] = -Bv[1];
@@ -523,7 +525,7 @@ __global__ __launch_bounds__(256) void k3_stage(Args3 a, int st) {
     if (is_full3(fc.scheme))   // already in the face frame
         for (int m = 0; m < 5; ++m) Vl[m] = a.V[((size_t)s * 5 + m) * R + r];
     double rl[5];
-    char_rate3(U, dn, yp, ym, zp, zm, Vl, U0, fc.scheme, fc.K, fc.alpha, fc.Pinf, rl);
+    char_rate3(U, dn, yp, ym, zp, zm, Vl, U0[1], sqrt(GAMMA * L3::cs2 * U0[4]), fc.scheme, fc.K, fc.alpha, fc.Pinf, rl);
     rl[1] *= fc.sn;   // back to global components
     for (int m = 0; m < 5; ++m) {
         const size_t o = iub(R, jj, m, r);
@@ -533,16 +535,102 @@ __global__ __launch_bounds__(256) void k3_stage(Args3 a, int st) {
     }
 }
 
+// The coupled face system's four RK4 stages and, with the equilibrium BC, the new layer populations.  A
+// work-group takes an 8 x 8 tile of a face's rows and the four rows of halo around it that the stages
+// need (a stage couples a row to its neighbours in y and z): 16 x 16 rows, one thread per row and layer
+// (768, a wavefront in one layer), the stage inputs in LDS in the face frame, double-buffered, so a
+// stage takes one barrier; its rates are computed 3 - st rows around the tile.  Bulk values at stage
+// time t + theta: (1 - theta) strip^n + theta strip^{n+1}.
+// Against one launch per stage: the rates are computed 2.2 times, but a stage's input and the running
+// sum go neither through memory nor through a launch.  Bound by the chain of one tile (16 us of loads, four
+// stages at three wavefronts a SIMD, reconstruction); its share of the step on 61 x 90 x 47, faces normal to y,
+// went from 33 to 16 us and the step from 97 to 80 us.  On large faces the stage launches are faster
+// (see launch_step3).
+constexpr int RK3_T = 8, RK3_W = RK3_T + 8, RK3_N = RK3_W * RK3_W;
+template <typename T>
+__global__ __launch_bounds__(RK3_N* L3::M) void k3_rk4(Args3 a, T* __restrict__ S) {
+    __shared__ double sY[2][L3::M][5][RK3_N];
+    const int s = blockIdx.y;
+    const Face3& fc = a.f[s];
+    if (!is_char3(fc.scheme)) return;
+    const int nty = (a.ny + RK3_T - 1) / RK3_T;
+    const int tz = (int)blockIdx.x / nty, ty = (int)blockIdx.x - tz * nty;
+    const int jj = (int)threadIdx.x / RK3_N, p = (int)threadIdx.x - jj * RK3_N;
+    const int ly = p % RK3_W, lz = p / RK3_W;
+    // the tile's rows with the periodic images around them: any ny, nz >= 1
+    auto wrapm = [](int v, int n) { v %= n; return v < 0 ? v + n : v; };
+    const int yo = ty * RK3_T + ly - 4, zo = tz * RK3_T + lz - 4;
+    const int R = a.rows, r = wrapm(zo, a.nz) * a.ny + wrapm(yo, a.ny);
+    const double sn = fc.sn;
+    const double* ub = (const double*)(a.reg_cur + fc.off_ub);
+    const double* sc = (const double*)(a.reg_cur + fc.off_strip);
+    const double* sx = (const double*)(a.reg_next + fc.off_strip);
+    const bool full = is_full3(fc.scheme);
+    double U0[5], Y[5], acc[5], Vl[5] = {0, 0, 0, 0, 0}, x0[5], x1[5];
+    for (int m = 0; m < 5; ++m) {
+        U0[m] = ub[iub(R, jj, m, r)];
+        x0[m] = jj == 0 ? sc[(size_t)m * R + r] : 0.0;
+        x1[m] = jj == 0 ? sx[(size_t)m * R + r] : 0.0;
+        if (full) Vl[m] = a.V[((size_t)s * 5 + m) * R + r];   // already in the face frame
+    }
+    U0[1] *= sn; x0[1] *= sn; x1[1] *= sn;
+    for (int m = 0; m < 5; ++m) {
+        Y[m] = acc[m] = U0[m];
+        sY[0][jj][m][p] = U0[m];
+    }
+    __syncthreads();
+    const double thv[4] = {0.0, 0.5, 0.5, 1.0}, bst[4] = {1.0, 2.0, 2.0, 1.0};
+    const double s0 = sqrt(GAMMA * L3::cs2 * U0[4]);
+    const int rim = min(min(ly, RK3_W - 1 - ly), min(lz, RK3_W - 1 - lz));   // rows to the halo's edge
+#pragma unroll 1
+    for (int st = 0; st < 4; ++st) {
+        const double th = thv[st];
+        if (rim > st) {
+            const double(*Ys)[5][RK3_N] = sY[st & 1];
+            double dn[5], yp[5], ym[5], zp[5], zm[5], rl[5];
+            for (int m = 0; m < 5; ++m) {
+                // eq. FD-dx-bw at the outermost layer, eq. FD-dx-center below it
+                const double in = jj == 0 ? (1.0 - th) * x0[m] + th * x1[m] : Ys[jj - 1][m][p];
+                dn[m] = jj == L3::M - 1 ? 0.5 * (3.0 * Y[m] - 4.0 * in + Ys[jj - 2][m][p]) : 0.5 * (Ys[jj + 1][m][p] - in);
+                yp[m] = Ys[jj][m][p + 1];
+                ym[m] = Ys[jj][m][p - 1];
+                zp[m] = Ys[jj][m][p + RK3_W];
+                zm[m] = Ys[jj][m][p - RK3_W];
+            }
+            char_rate3(Y, dn, yp, ym, zp, zm, Vl, U0[1], s0, fc.scheme, fc.K, fc.alpha, fc.Pinf, rl);
+            for (int m = 0; m < 5; ++m) {
+                acc[m] += bst[st] * (1.0 / 6.0) * rl[m];
+                if (st < 3) {
+                    Y[m] = U0[m] + thv[st + 1] * rl[m];
+                    sY[(st & 1) ^ 1][jj][m][p] = Y[m];
+                }
+            }
+        }
+        if (st < 3) __syncthreads();
+    }
+    if (rim < 4 || yo >= a.ny || zo >= a.nz) return;
+    acc[1] *= sn;   // back to global components
+    double* ubn = (double*)(a.reg_next + fc.off_ub);
+    for (int m = 0; m < 5; ++m) ubn[iub(R, jj, m, r)] = acc[m];
+    if (fc.meso == 1) return;   // k3_final
+    double fe[L3::Q];
+    feq3_dev<double>(acc[0] - 1.0, acc[1], acc[2], acc[3], acc[4] - 1.0, fe);
+    T* o = S + (((size_t)s * R + r) * L3::M + jj) * L3::Q;
+#pragma unroll
+    for (int i = 0; i < L3::Q; ++i) o[i] = (T)fe[i];
+}
+
 // New layer populations, three threads per face row (one per layer; neighbouring x of the same
 // row, so the stores of a plane cover contiguous bytes): the equilibrium of U_b^{n+1}, plus with
 // NEEP (eq. NEEP) the post-collision non-equilibrium part of x_f; zero-gradient faces copy x_f
-// (eq. zg-bc) from the new bulk populations in B.
+// (eq. zg-bc) from the new bulk populations in B.  eq: 0 where k3_rk4 has written the layers of faces
+// with the equilibrium BC.
 template <typename T>
-__global__ __launch_bounds__(256) void k3_final(const T* __restrict__ A, T* __restrict__ S, Args3 a) {
+__global__ __launch_bounds__(256) void k3_final(const T* __restrict__ A, T* __restrict__ S, Args3 a, int eq) {
     const int s = blockIdx.y;
     const Face3& fc = a.f[s];
     const int t = blockIdx.x * 256 + threadIdx.x;
-    if (fc.scheme == F3_PERIODIC || t >= L3::M * a.rows) return;
+    if (fc.scheme == F3_PERIODIC || t >= L3::M * a.rows || (!eq && is_char3(fc.scheme) && fc.meso != 1)) return;
     const int r = t / L3::M, jj = t - L3::M * r;
     const int y = r % a.ny, z = r / a.ny;
     T* o = S + (((size_t)s * a.rows + r) * L3::M + jj) * L3::Q;

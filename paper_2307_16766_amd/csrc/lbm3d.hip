@@ -212,24 +212,39 @@ int launch_step3(lbm3d_ctx* c) {
     const Args3 a = make_args3(c);
     const Bulk3 g = make_bulk3(c);
     const int rows = c->L.rows;
+    T* lay = (T*)(c->ws + c->L.off_lay);
     const int bpr = (g.nx + 255) / 256;
     const unsigned magic = bpr > 1 ? (unsigned)((1ull << 32) / (unsigned long long)bpr + 1ull) : 0u;
     const unsigned nblk = (unsigned)bpr * (unsigned)rows;
     // faces first (they read only A): characteristic solve, then the layers' new populations,
     // staged for the bulk kernel's boundary-layer lanes
     if (!a.xper) {
+        // The faces' solve in one launch of tiles while its work-groups (one per CU, as long as a tile's
+        // chain each) take at most four rounds of the 256 CUs: beside the four stage launches and k3_final
+        // it takes 16 against 33 us on 61 x 47 rows a face (FP64), 19 against 34 on 64 x 128, 54 against 65 on
+        // 192 x 128 (768 work-groups), but 139 against 129 on 256 x 256 (2048), where the stages keep the
+        // memory busy.
+        const int ntile = ((a.ny + RK3_T - 1) / RK3_T) * ((a.nz + RK3_T - 1) / RK3_T);
+        const bool tiled = 2 * ntile <= 4 * 256;
         if (c->cfg.bc[0] != LBM_BC_ZG || c->cfg.bc[1] != LBM_BC_ZG) {
             hipLaunchKernelGGL((k3_prep<T>), dim3((4 * rows + 255) / 256, 2), dim3(256), 0, c->stream, A,
                                g.strip ? (const T*)g.strip : nullptr, c->L.sm, a);
             HIPCHK3(c, hipGetLastError());
-            for (int st = 0; st < 4; ++st) {
+            if (tiled) {
+                hipLaunchKernelGGL((k3_rk4<T>), dim3(ntile, 2), dim3(RK3_N * L3::M), 0, c->stream, a, lay);
+                HIPCHK3(c, hipGetLastError());
+            }
+            for (int st = 0; st < 4 && !tiled; ++st) {
                 hipLaunchKernelGGL(k3_stage, dim3((L3::M * rows + 255) / 256, 2), dim3(256), 0, c->stream, a, st);
                 HIPCHK3(c, hipGetLastError());
             }
         }
-        hipLaunchKernelGGL((k3_final<T>), dim3((L3::M * rows + 255) / 256, 2), dim3(256), 0, c->stream, A,
-                           (T*)(c->ws + c->L.off_lay), a);
-        HIPCHK3(c, hipGetLastError());
+        bool final = !tiled;   // else only for layers that take the populations of x_f
+        for (int s = 0; s < 2; ++s) final = final || a.f[s].scheme == F3_ZG || a.f[s].meso == 1;
+        if (final) {
+            hipLaunchKernelGGL((k3_final<T>), dim3((L3::M * rows + 255) / 256, 2), dim3(256), 0, c->stream, A, lay, a, tiled ? 0 : 1);
+            HIPCHK3(c, hipGetLastError());
+        }
     }
     const bool rec = c->timing > 0 && (c->tcalls++ % (size_t)c->timing) == 0 && c->tcount < 65536;
     if (rec) {
