@@ -13,6 +13,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "adjoint.h"
@@ -302,7 +303,8 @@ struct lbm_ctx {
     double* inlet[4] = {nullptr, nullptr, nullptr, nullptr};
     int inlet_set[4] = {0, 0, 0, 0};   // Dirichlet profile given by lbm_dirichlet_profile
     double* diag = nullptr;
-    int cur = 0;
+    int cur = 0;                   // f[cur], region[cur] hold the current level: every step changes it
+    bool captured = false;         // a call was captured into a graph (note_capture)
     long steps = 0;
     int diag_every = 0;            // lbm_step checks for non-finite populations every n steps (0: off)
     int device = 0;                // HIP device current at lbm_init
@@ -507,7 +509,9 @@ int launch_pair(lbm_ctx* c) {
         else hipLaunchKernelGGL((k_pair<Q, T, false, false>), grid, block, 0, s, A, B, g);
     };
     HIPCHK(c, timed_launch(c, 2, pass));
-    c->cur ^= 1;
+    // level n + 2 belongs to the parity of level n: the buffers change places
+    std::swap(c->f[0], c->f[1]);
+    std::swap(c->region[0], c->region[1]);
     c->steps += 2;
     return LBM_OK;
 }
@@ -782,6 +786,18 @@ int dispatch(const lbm_ctx* c, F&& f) {
     return c->cfg.precision == LBM_FP64 ? f.template operator()<37, double>() : f.template operator()<37, float>();
 }
 
+// A captured graph holds the addresses of the buffers that a call read and wrote.  It can be replayed,
+// and be mixed with calls of an even number of steps, as long as such calls leave the state in the same
+// buffer: single steps do, and passes do in even numbers, so that a context on which a call was
+// captured takes no others from then on.  Nothing can be captured on the null stream.
+int note_capture(lbm_ctx* c) {
+    if (c->captured || !c->stream) return LBM_OK;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    HIPCHK(c, hipStreamIsCapturing(c->stream, &st));
+    c->captured = st != hipStreamCaptureStatusNone;
+    return LBM_OK;
+}
+
 // Diagnostics of the current state into d_out[8] (device), on the context's stream: the first
 // pass writes nparts partials per quantity into `partials` (component-major, [8][nparts]), each
 // work-group covering tpw consecutive 256-node row tiles (tpw = 1: one tile each, nparts = the
@@ -948,12 +964,17 @@ int lbm_dirichlet_profile(lbm_ctx* c, int side, const double* d_U) {
 int lbm_step(lbm_ctx* c, int nsteps) {
     if (!c) return fail(nullptr, LBM_E_ARG, "null context");
     if (nsteps < 0) return fail(c, LBM_E_ARG, "nsteps < 0");
+    if (note_capture(c) != LBM_OK) return LBM_E_HIP;
     for (int k = 0; k < nsteps;) {
-        // two steps at once, unless a check falls between them
-        const bool two = c->L.pair.use && k + 1 < nsteps && !(c->diag_every > 0 && (c->steps + 1) % c->diag_every == 0);
-        const int rc = dispatch(c, [&]<int Q, typename T>() -> int { return two ? launch_pair<Q, T>(c) : launch_step<Q, T>(c); });
-        if (rc != LBM_OK) return rc;
-        k += two ? 2 : 1;
+        // up to the next check or the end of the call: passes of two steps, the rest singly
+        const int m = c->diag_every > 0 ? (int)std::min<long>(nsteps - k, c->diag_every - c->steps % c->diag_every) : nsteps - k;
+        int passes = c->L.pair.use ? m / 2 : 0;
+        if (c->captured) passes &= ~1;
+        for (int j = 0; j < m - passes; ++j) {
+            const int rc = dispatch(c, [&]<int Q, typename T>() -> int { return j < passes ? launch_pair<Q, T>(c) : launch_step<Q, T>(c); });
+            if (rc != LBM_OK) return rc;
+        }
+        k += m;
         if (c->diag_every > 0 && c->steps % c->diag_every == 0) {
             double out[8];
             const int rd = host_diag(c, out);
@@ -968,6 +989,7 @@ int lbm_step(lbm_ctx* c, int nsteps) {
 int lbm_macroscopic(lbm_ctx* c, double* rho, double* ux, double* uy, double* Tf) {
     if (!c) return fail(nullptr, LBM_E_ARG, "null context");
     if (!rho || !ux || !uy) return fail(c, LBM_E_ARG, "output pointer is NULL");
+    if (note_capture(c) != LBM_OK) return LBM_E_HIP;
     const int n = c->cfg.nx * c->cfg.ny;
     return dispatch(c, [&]<int Q, typename T>() -> int {
         hipLaunchKernelGGL((k_macro<Q, T>), dim3((n + 255) / 256), dim3(256), 0, c->stream, (const T*)c->f[c->cur],
@@ -982,6 +1004,7 @@ int lbm_boundary_state(lbm_ctx* c, int side, double* d_out) {
     if (side < 0 || side > 3 || !d_out) return fail(c, LBM_E_ARG, "bad side or output pointer");
     const SideDev& s = c->L.s[side];
     if (s.kind != KIND_CHAR) return fail(c, LBM_E_STATE, "side is not a characteristic side");
+    if (note_capture(c) != LBM_OK) return LBM_E_HIP;
     HIPCHK(c, hipMemcpyAsync(d_out, c->region[c->cur] + s.off_ub, (size_t)c->L.M * s.len * 4 * 8, hipMemcpyDeviceToDevice, c->stream));
     return LBM_OK;
 }
@@ -1000,6 +1023,7 @@ int lbm_diagnostics(lbm_ctx* c, double* h_out) {
 int lbm_diagnostics_noalloc(lbm_ctx* c, double* d_out) {
     if (!c) return fail(nullptr, LBM_E_ARG, "null context");
     if (!d_out) return fail(c, LBM_E_ARG, "output pointer is NULL");
+    if (note_capture(c) != LBM_OK) return LBM_E_HIP;
     int dev = -1;
     HIPCHK(c, hipGetDevice(&dev));
     if (dev != c->device || !c->scratch) return fail(c, LBM_E_STATE, "the context's device is not the current device");
@@ -1092,6 +1116,7 @@ int lbm_record(lbm_ctx* c, int nsteps, int every, void* d_tape, size_t tape_byte
     tape_layout(c->L, c->cfg.nx, c->cfg.ny, nsteps, std::min(every, nsteps), t);
     if (tape_bytes < t.total) return fail(c, LBM_E_ARG, "tape smaller than lbm_tape_bytes");
     t.base = (char*)d_tape;
+    if (note_capture(c) != LBM_OK) return LBM_E_HIP;
     // The reverse sweep starts with the last segments: their steps write what a recomputation from
     // the checkpoint would (moments, boundary states and stage inputs of every level) into the two
     // recomputation sets at once (1 us more per step than a plain one), so that the first sweep has
