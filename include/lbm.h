@@ -151,7 +151,7 @@ int lbm_dirichlet_profile(lbm_ctx* ctx, int side, const double* d_U);
  * call synchronises the stream there); when it is positive lbm_step stops and returns
  * LBM_E_NONFINITE, with the state of that step kept and lbm_steps_done telling which step.
  * On large grids two steps are taken per pass over the populations (not across such a check);
- * the result is that of single steps up to rounding.  The call only launches kernels (with the
+ * the result is that of single steps bit for bit, however a run is split into calls.  The call only launches kernels (with the
  * check off): captured into a graph, an even number of steps can be replayed, each replay
  * advancing the state, and be mixed with calls of an even number of steps. */
 int lbm_step(lbm_ctx* ctx, int nsteps);

@@ -37,6 +37,8 @@
 
 #include "kernels.h"
 
+#pragma clang fp contract(fast)   // the reverse sweep advances no state
+
 namespace lbm {
 
 // ------------------------------------------------------------------ per-node adjoint pieces
@@ -1432,3 +1434,5 @@ __global__ __launch_bounds__(1024) void k_adj_final(AdjArgs g) {
 }
 
 }  // namespace lbm
+
+#pragma clang fp contract(on)

@@ -13,9 +13,17 @@
 // Library order: index 0 is the rest velocity, 1..NP a set of velocities no two of which are
 // opposite, NP+1..2NP their opposites (c_{p+NP} = -c_p).  The equilibrium is evaluated per
 // opposite pair from its even and odd parts in a = xi.u (one polynomial for both members).
+//
+// Products are fused with the sums they enter inside one expression only (and always there), not
+// across statements: across statements the choice follows the basic blocks, so that two kernels
+// would round the same function differently.  Whatever advances a state goes through the functions
+// of this file and of kernels.h, so a step gives the same bits in a pass of two steps, singly, or
+// while it is recorded, and a run does not depend on how it is split into calls.
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#pragma clang fp contract(on)
 
 namespace lbm {
 
@@ -153,24 +161,25 @@ __device__ __forceinline__ void feq_group(int g, R u2, R th, R& C0, R& C1, R& D0
         D0 = R(1);
     }
 }
-// E and O of a pair with a = xi.u/cs
+// H - 1 of both members of a pair with a = xi.u/cs: E + a O and E - a O
 template <int Q, typename R>
-__device__ __forceinline__ void feq_pair(R a, R C0, R C1, R D0, R& E, R& O) {
+__device__ __forceinline__ void feq_pair(R a, R C0, R C1, R D0, R& hp, R& hm) {
     using L = Lat<Q>;
     const R a2 = a * a;
-    if (L::order == 4) {
-        E = C0 + a2 * (C1 + a2 * R(1.0 / 24.0));
-        O = a * (D0 + a2 * R(1.0 / 6.0));
-    } else if (L::order == 3) {
-        E = C0 + a2 * C1;
-        O = a * (D0 + a2 * R(1.0 / 6.0));
+    if (L::order == 2) {
+        const R E = C0 + C1 * a2;
+        hp = E + a;
+        hm = E - a;
     } else {
-        E = C0 + C1 * a2;
-        O = a;
+        const R E = L::order == 4 ? C0 + a2 * (C1 + a2 * R(1.0 / 24.0)) : C0 + a2 * C1;
+        const R O = D0 + a2 * R(1.0 / 6.0);
+        hp = E + a * O;
+        hm = E - a * O;
     }
 }
-template <int Q, typename R>
-__device__ __forceinline__ void feq_dev(R rm1, R ux, R uy, R th, R* fe) {
+// f(i, w_i, h_i) for every velocity, the equilibrium deviation being w_i h_i
+template <int Q, typename R, typename F>
+__device__ __forceinline__ void feq_each(R rm1, R ux, R uy, R th, F&& f) {
     using L = Lat<Q>;
     const R rho = R(1) + rm1;
     const R ics = R(1.0 / L::cs);
@@ -179,17 +188,20 @@ __device__ __forceinline__ void feq_dev(R rm1, R ux, R uy, R th, R* fe) {
     R C0[L::NG], C1[L::NG], D0[L::NG];
 #pragma unroll
     for (int g = 0; g < L::NG; ++g) feq_group<Q, R>(g, u2, th, C0[g], C1[g], D0[g]);
-    fe[0] = R(L::wg(0)) * (rm1 + rho * C0[0]);
+    f(0, R(L::wg(0)), rm1 + rho * C0[0]);
 #pragma unroll
     for (int p = 1; p <= L::NP; ++p) {
         const int g = L::grp(p);
         const R a = (R(L::pcx(p)) * vx + R(L::pcy(p)) * vy) * ics;
-        R E, O;
-        feq_pair<Q, R>(a, C0[g], C1[g], D0[g], E, O);
-        const R w = R(L::wg(g));
-        fe[p] = w * (rm1 + rho * (E + O));
-        fe[p + L::NP] = w * (rm1 + rho * (E - O));
+        R hp, hm;
+        feq_pair<Q, R>(a, C0[g], C1[g], D0[g], hp, hm);
+        f(p, R(L::wg(g)), rm1 + rho * hp);
+        f(p + L::NP, R(L::wg(g)), rm1 + rho * hm);
     }
+}
+template <int Q, typename R>
+__device__ __forceinline__ void feq_dev(R rm1, R ux, R uy, R th, R* fe) {
+    feq_each<Q, R>(rm1, ux, uy, th, [&](int i, R w, R h) { fe[i] = w * h; });
 }
 
 // BGK collision (eq. bgk) in deviation form: d* = d + omega (de - d), omega = 1/tau.
@@ -228,11 +240,11 @@ __device__ __forceinline__ void collide_pairs(float* d, float omega) {
     for (int p = 1; p <= NP; ++p) {
         const int g = L::grp(p);
         const float a = (float(L::pcx(p)) * vx + float(L::pcy(p)) * vy) * ics;
-        float E, O;
-        feq_pair<Q, float>(a, C0[g], C1[g], D0[g], E, O);
+        float hp, hm;
+        feq_pair<Q, float>(a, C0[g], C1[g], D0[g], hp, hm);
         const float w = float(L::wg(g));
-        x[p] = w * (rm1 + rho * (E + O)) - d[p];
-        x[p + NP] = w * (rm1 + rho * (E - O)) - d[p + NP];
+        x[p] = w * (rm1 + rho * hp) - d[p];
+        x[p + NP] = w * (rm1 + rho * hm) - d[p + NP];
         const float o = x[p] - x[p + NP];
         ge[g] += x[p] + x[p + NP];
         if (L::pcx(p) != 0) mx += float(L::pcx(p)) * o;
@@ -271,10 +283,7 @@ __device__ __forceinline__ void collide_dev(R* d, R omega) {
     }
     R rm1, ux, uy, th;
     moments_dev<Q, R>(d, rm1, ux, uy, th);
-    R fe[Q];
-    feq_dev<Q, R>(rm1, ux, uy, th, fe);
-#pragma unroll
-    for (int i = 0; i < Q; ++i) d[i] = d[i] + omega * (fe[i] - d[i]);
+    feq_each<Q, R>(rm1, ux, uy, th, [&](int i, R w, R h) { d[i] = d[i] + omega * (w * h - d[i]); });
 }
 
 }  // namespace lbm
