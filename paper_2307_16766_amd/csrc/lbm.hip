@@ -304,6 +304,7 @@ struct lbm_ctx {
     int inlet_set[4] = {0, 0, 0, 0};   // Dirichlet profile given by lbm_dirichlet_profile
     double* diag = nullptr;
     int cur = 0;                   // f[cur], region[cur] hold the current level: every step changes it
+    bool region_lost = false;      // a failed lbm_record could not copy region[cur] back: until lbm_restore
     bool captured = false;         // a call was captured into a graph (note_capture)
     long steps = 0;
     int diag_every = 0;            // lbm_step checks for non-finite populations every n steps (0: off)
@@ -786,6 +787,10 @@ int dispatch(const lbm_ctx* c, F&& f) {
     return c->cfg.precision == LBM_FP64 ? f.template operator()<37, double>() : f.template operator()<37, float>();
 }
 
+int region_state(lbm_ctx* c) {
+    return c->region_lost ? fail(c, LBM_E_STATE, "the boundary state was lost in a failed lbm_record (lbm_restore brings one back)") : LBM_OK;
+}
+
 // A captured graph holds the addresses of the buffers that a call read and wrote.  It can be replayed,
 // and be mixed with calls of an even number of steps, as long as such calls leave the state in the same
 // buffer: single steps do, and passes do in even numbers, so that a context on which a call was
@@ -964,6 +969,7 @@ int lbm_dirichlet_profile(lbm_ctx* c, int side, const double* d_U) {
 int lbm_step(lbm_ctx* c, int nsteps) {
     if (!c) return fail(nullptr, LBM_E_ARG, "null context");
     if (nsteps < 0) return fail(c, LBM_E_ARG, "nsteps < 0");
+    if (region_state(c) != LBM_OK) return LBM_E_STATE;
     if (note_capture(c) != LBM_OK) return LBM_E_HIP;
     for (int k = 0; k < nsteps;) {
         // up to the next check or the end of the call: passes of two steps, the rest singly
@@ -1004,6 +1010,7 @@ int lbm_boundary_state(lbm_ctx* c, int side, double* d_out) {
     if (side < 0 || side > 3 || !d_out) return fail(c, LBM_E_ARG, "bad side or output pointer");
     const SideDev& s = c->L.s[side];
     if (s.kind != KIND_CHAR) return fail(c, LBM_E_STATE, "side is not a characteristic side");
+    if (region_state(c) != LBM_OK) return LBM_E_STATE;
     if (note_capture(c) != LBM_OK) return LBM_E_HIP;
     HIPCHK(c, hipMemcpyAsync(d_out, c->region[c->cur] + s.off_ub, (size_t)c->L.M * s.len * 4 * 8, hipMemcpyDeviceToDevice, c->stream));
     return LBM_OK;
@@ -1051,6 +1058,7 @@ size_t lbm_state_bytes(const lbm_ctx* c) {
 int lbm_save(lbm_ctx* c, void* d_buf) {
     if (!c) return fail(nullptr, LBM_E_ARG, "null context");
     if (!d_buf) return fail(c, LBM_E_ARG, "buffer is NULL");
+    if (region_state(c) != LBM_OK) return LBM_E_STATE;
     char* b = (char*)d_buf;
     c->save_hdr[0] = c->steps;
     for (int s = 0; s < 4; ++s) c->save_hdr[1 + s] = c->inlet_set[s];
@@ -1080,6 +1088,7 @@ int lbm_restore(lbm_ctx* c, const void* d_buf) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
     c->cur = 0;
     c->steps = hdr[0];
+    c->region_lost = false;
     for (int s = 0; s < 4; ++s) c->inlet_set[s] = (int)hdr[1 + s];
     c->tape = Tape();
     // the step kernel never writes the layers of a Dirichlet side: both population buffers get
@@ -1112,6 +1121,7 @@ int lbm_record(lbm_ctx* c, int nsteps, int every, void* d_tape, size_t tape_byte
     if (nsteps < 1 || every < 1) return fail(c, LBM_E_ARG, "nsteps and every must be positive");
     if (!d_tape || ((uintptr_t)d_tape % ALIGN) != 0) return fail(c, LBM_E_ARG, "tape must be non-NULL and 256-byte aligned");
     if (c->steps != 0) return fail(c, LBM_E_STATE, "recording starts from the initial state (no steps taken)");
+    if (region_state(c) != LBM_OK) return LBM_E_STATE;
     Tape t;
     tape_layout(c->L, c->cfg.nx, c->cfg.ny, nsteps, std::min(every, nsteps), t);
     if (tape_bytes < t.total) return fail(c, LBM_E_ARG, "tape smaller than lbm_tape_bytes");
@@ -1125,7 +1135,7 @@ int lbm_record(lbm_ctx* c, int nsteps, int every, void* d_tape, size_t tape_byte
     // 40 steps of D2Q17 on 131 x 75 in three: 2339 -> 2099 us.
     const size_t rbytes = c->L.region_bytes;
     char* reg = nullptr;   // the boundary state of the current level where it is in a set's slot
-    for (int n = 0; n < nsteps; ++n) {
+    auto advance = [&](int n) -> int {
         const int seg = n / t.K, j = n - seg * t.K, b = seg & 1;
         const bool keep = seg >= t.nchk - 2;
         if (j == 0) {
@@ -1134,12 +1144,13 @@ int lbm_record(lbm_ctx* c, int nsteps, int every, void* d_tape, size_t tape_byte
             HIPCHK(c, hipMemcpyAsync(chk, c->f[c->cur], c->L.f_bytes, hipMemcpyDeviceToDevice, c->stream));
             HIPCHK(c, hipMemcpyAsync(chk + c->L.f_bytes, at, rbytes, hipMemcpyDeviceToDevice, c->stream));
             if (keep) {
-                reg = t.reg_slot(c->L, b, 0);
-                HIPCHK(c, hipMemcpyAsync(reg, at, rbytes, hipMemcpyDeviceToDevice, c->stream));
+                char* slot = t.reg_slot(c->L, b, 0);
+                HIPCHK(c, hipMemcpyAsync(slot, at, rbytes, hipMemcpyDeviceToDevice, c->stream));
+                reg = slot;
                 t.kept[b] = seg;
             }
         }
-        const int rc = dispatch(c, [&]<int Q, typename T>() -> int {
+        return dispatch(c, [&]<int Q, typename T>() -> int {
             if (!keep) return launch_step<Q, T>(c);
             const int bpr = (c->cfg.nx + 255) / 256;
             const T* A = (const T*)c->f[c->cur];
@@ -1156,12 +1167,17 @@ int lbm_record(lbm_ctx* c, int nsteps, int every, void* d_tape, size_t tape_byte
             c->steps += 1;
             return LBM_OK;
         });
-        if (rc != LBM_OK) {   // the context stays at the last step taken
-            if (reg) (void)hipMemcpyAsync(c->region[c->cur], reg, rbytes, hipMemcpyDeviceToDevice, c->stream);
-            return rc;
+    };
+    int rc = LBM_OK;
+    for (int n = 0; n < nsteps && rc == LBM_OK; ++n) rc = advance(n);
+    if (reg) {   // whatever failed: the context stays at the last step taken
+        const hipError_t e = hipMemcpyAsync(c->region[c->cur], reg, rbytes, hipMemcpyDeviceToDevice, c->stream);
+        if (e != hipSuccess) {
+            c->region_lost = true;
+            if (rc == LBM_OK) rc = fail(c, LBM_E_HIP, std::string("copy of the boundary state: ") + hipGetErrorString(e));
         }
     }
-    HIPCHK(c, hipMemcpyAsync(c->region[c->cur], reg, rbytes, hipMemcpyDeviceToDevice, c->stream));
+    if (rc != LBM_OK) return rc;
     t.step_end = c->steps;
     c->tape = t;
     return LBM_OK;
