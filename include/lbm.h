@@ -116,6 +116,10 @@ typedef struct lbm_ctx lbm_ctx;
  * Returns 0 for an invalid configuration. */
 size_t lbm_workspace_bytes(const lbm_config* cfg);
 
+/* Steps that lbm_step takes per pass over the populations on this configuration: 2 on large
+ * grids, 1 elsewhere, 0 for an invalid configuration. */
+int lbm_steps_per_pass(const lbm_config* cfg);
+
 /* Create a context and set the initial state f = f^eq(rho0, u0, T0) at every node (Sec. 2,
  * "Initialize"); boundary states start from the same fields.  d_workspace: device buffer of
  * at least lbm_workspace_bytes(cfg) bytes, 256-byte aligned.  hip_stream: hipStream_t (NULL

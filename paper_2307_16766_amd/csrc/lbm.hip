@@ -158,15 +158,40 @@ int validate(const lbm_config* c, std::string& err) {
 // sides whose layers change with time: their level n + 1 goes through a band buffer
 bool band_side(int b) { return is_char(b) || b == BC_ZG; }
 
-// Whether lbm_step takes two steps per pass on this grid, and the pass's tiles.  A segment recomputes
-// 2 M rows and starts cold, so it needs some rows of its own: 3 M + 1, where the pass is still the
-// faster one (per step, periodic boxes: D2Q37 FP32 1024 x 512, 10 rows, 30.2 -> 28.4 us; FP64 700 x 500,
-// 11 rows, 39.5 -> 27.6 us; D2Q9 FP32 1023 x 700, 6 rows, 13.7 -> 8.2 us).  Boundaries cost two launches
-// per pass that nothing hides (about 20 us each for M = 3, 6 us for M = 1), which the saved traffic has
-// to pay for: the bytes of one single step from which it does (LODI-RELAX / CBC-RELAX sides, per step:
-// D2Q37 FP32 1500 x 1000 (444 MB) 79.5 -> 75.9 us, 1024 x 1024 (310 MB) 58.0 -> 62.1; FP64 1024 x 512
-// (310 MB) 58.7 -> 56.1, 700 x 500 (207 MB) 40.7 -> 42.6; D2Q17 FP32 2048 x 1024 (285 MB) equal; FP64
-// 1500 x 1000 (408 MB) 76.1 -> 60.2; D2Q9 FP32 1500 x 1000 (108 MB) 25.1 -> 21.8).
+// rows per work-group of side s's solve in k_bnd: nothing hides that launch, so the chunks are short
+// whatever the grid (see chunk_rows_x)
+int pair_rows(int M, int s, int b) { return s < 2 ? short_rows_x(M, is_full(b)) : chunk_rows(M) / 2; }
+
+// Whether lbm_step takes two steps per pass on this grid, and the pass's tiles.
+//
+// A row of a tile costs its work-group the same however many of its columns lie in the grid, and a
+// segment of `seg` rows takes seg + 2 M of them (2 M recomputed), at least 3 M + 1 of its own.  So what
+// counts is the share of its thread rows that a pass spends on output nodes of the grid:
+//   share = nx rows / (work-group slots (seg + 2 M) nt).
+// Measured on periodic boxes of 24 to 600 columns, us per step in passes against single steps: D2Q37
+// FP32 64 x 8000 (share 0.21) 50.4 : 28.5, 125 x 3000 (0.32) 25.0 : 23.5, 241 x 3000 (0.37) 42.9 : 42.1,
+// 481 x 1000 (0.41) 27.1 : 29.3, 300 x 2000 (0.42) 33.2 : 42.6; FP64 40 x 8000 (0.26) 45.8 : 42.7, 121 x 1300
+// (0.28) 22.7 : 21.9, 136 x 1300 (0.32) 23.1 : 24.0, 121 x 3000 (0.37) 40.7 : 44.6; D2Q17 FP64 64 x 8000
+// (0.21) 31.8 : 26.5, 90 x 5000 (0.26) 23.8 : 26.5; FP32 64 x 8000 (0.18) 19.4 : 16.1, 100 x 8000 (0.28)
+// faster; D2Q9 is twice as fast at every share.
+//
+// Boundaries cost two launches per pass that nothing hides, as long as one chunk's chain (13 to 17 us
+// for M = 3, 6 us for M = 1) while their chunks are resident at once (448), and in proportion above that;
+// the saved traffic has to pay for them: `least`, the bytes of a single step from which it does.
+// Measured with one or two pairs of LODI-RELAX, LODI and CBC-RELAX sides at 1.02 and 1.6 times the bytes,
+// shares from 0.09 to 1 and up to 20 times the resident chunks, in passes against single steps: D2Q37 FP64
+// 64 x 8077 (0.42) 116.6 : 97.3, 250 x 2068 (0.51) 70.7 : 65.2, 500 x 1034 (0.58) 57.8 : 59.7, 1293 x 400
+// (0.65) 54.7 : 58.7, but 100 x 8109 (0.65, 1690 chunks) 132.4 : 127.9; FP32 130 x 11664 (0.45) 166 : 144,
+// 750 x 3172 (0.65, 661 chunks) 135.9 : 131.1, 2022 x 750 (0.70) 70.9 : 77.8; D2Q17 FP64 500 x 1801 (0.49)
+// 47.9 : 45.6, 750 x 1201 (0.55) 42.4 : 44.1; FP32 1651 x 1500 (337 MB) 58.7 : 56.3, 2589 x 1500 (528 MB)
+// 81.8 : 86.5; D2Q9 FP64 500 x 1559 (0.50) 25.1 : 22.9, 1559 x 500 (0.66) 21.7 : 21.9; FP32 250 x 9778
+// (0.46) 47.8 : 42.0, 3896 x 400 (0.74) 23.2 : 25.7.  A zero-gradient chunk is one long chain of strided
+// pulls and stores; for M = 3 it needs more (D2Q37 FP64 631 x 938 (350 MB) 85.1 : 65.5, 769 x 1417 (645 MB)
+// 0.99 times as fast, faster from 710 MB; FP32 614 x 4860 (883 MB) 0.97; D2Q17 FP64 5744 x 259 (405 MB)
+// 0.99; FP32 1476 x 3344 (671 MB) 1.00); so do, a little, chunks of 28 rows with viscous moments (CBC
+// sides normal to y: D2Q37 FP64 702 x 768 (319 MB) 58.6 : 57.4, 653 x 973 (376 MB) 68.8 : 67.3) and two CBC
+// sides normal to x (622 x 822 (303 MB) 60.8 : 57.6).  Of 4200 random grids, boundaries and reconstructions
+// that this rule gives to passes one was slower by more than 1.5 % (181 x 8465, 2.4 %).
 PairPlan pair_plan(const lbm_config* c) {
     const bool f64 = c->precision == LBM_FP64;
     PairPlan p = c->stencil == 9 ? (f64 ? pair_shape<9, double>() : pair_shape<9, float>())
@@ -178,9 +203,24 @@ PairPlan pair_plan(const lbm_config* c) {
     if (c->nx < 2 * p.bw || c->ny < 2 * p.bw || rows < 1) return p;
     p.ntx = ((xp ? c->nx : c->nx - M) + p.wo - 1) / p.wo;
     p.nseg = std::max(1, std::min(p.wgs / p.ntx, rows));
+    if (rows / p.nseg < 3 * M + 1) return p;
+    const double seg = (rows + p.nseg - 1) / p.nseg, rounds = (p.ntx * p.nseg + p.wgs - 1) / p.wgs;
+    const double share = (double)c->nx * rows / (rounds * p.wgs * (seg + 2 * M) * p.nt);
+    if (xp && yp) {
+        p.use = share >= (c->stencil == 9 ? 0.0 : c->stencil == 17 ? 0.25 : f64 ? 0.31 : 0.40);
+        return p;
+    }
+    double chunks = 0.0;
+    for (int s = 0; s < 4; ++s)
+        if (is_char(c->bc[s])) chunks += std::ceil((double)(s < 2 ? c->ny : c->nx) / pair_rows(M, s, c->bc[s]));
     const double bytes = 2.0 * c->stencil * (f64 ? 8 : 4) * c->nx * c->ny;
-    const double least = xp && yp ? 0.0 : c->stencil == 9 ? 110e6 : c->stencil == 17 ? (f64 ? 240e6 : 330e6) : (f64 ? 300e6 : 440e6);
-    p.use = rows / p.nseg >= 3 * M + 1 && bytes >= least;
+    const bool zg = c->bc[0] == BC_ZG || c->bc[1] == BC_ZG || c->bc[2] == BC_ZG || c->bc[3] == BC_ZG;
+    double least = c->stencil == 9 ? 110e6
+                 : zg ? (c->stencil == 17 ? (f64 ? 480e6 : 720e6) : (f64 ? 720e6 : 900e6))
+                      : (c->stencil == 17 ? (f64 ? 240e6 : 520e6) : (f64 ? 300e6 : 440e6));
+    if (is_full(c->bc[2]) || is_full(c->bc[3])) least *= 1.3;
+    else if (is_full(c->bc[0]) && is_full(c->bc[1])) least *= 1.1;
+    p.use = share >= (f64 ? 0.60 : 0.65) && bytes >= least * std::max(1.0, chunks / 448);
     return p;
 }
 
@@ -483,12 +523,11 @@ int launch_pair(lbm_ctx* c) {
     auto pass = [&](hipStream_t s) {
         if (nband > 0) {
             BndArgs a = make_bnd(c);
-            // nothing hides these launches: short chunks whatever the grid (see chunk_rows_x)
             int nbnd = 0;
             for (int k = 0; k < 4; ++k) {
                 SideDev& d = a.s[k];
                 if (d.kind == KIND_CHAR) {
-                    d.rows = d.nax == 0 ? short_rows_x(L.M, is_full(cfg.bc[k])) : chunk_rows(L.M) / 2;
+                    d.rows = pair_rows(L.M, k, cfg.bc[k]);
                     d.nblk = (d.len + d.rows - 1) / d.rows;
                 }
                 d.blk0 = nbnd;
@@ -846,6 +885,12 @@ size_t lbm_workspace_bytes(const lbm_config* cfg) {
     Layout L;
     make_layout(cfg, L);
     return L.total;
+}
+
+int lbm_steps_per_pass(const lbm_config* cfg) {
+    std::string err;
+    if (validate(cfg, err) != LBM_OK) { g_err = err; return 0; }
+    return pair_plan(cfg).use ? 2 : 1;
 }
 
 int lbm_init(const lbm_config* cfg, void* d_workspace, size_t workspace_bytes, void* hip_stream, const double* d_rho0,

@@ -22,7 +22,7 @@ RECON = {"equilibrium": 0, "neep": 1}
 VISC = {"meso": 0, "fd": 1}
 
 # exported symbols, as declared in include/lbm.h
-SYMBOLS = ["lbm_workspace_bytes", "lbm_init", "lbm_cbc_params", "lbm_reconstruction", "lbm_viscous", "lbm_dirichlet_profile", "lbm_step",
+SYMBOLS = ["lbm_workspace_bytes", "lbm_steps_per_pass", "lbm_init", "lbm_cbc_params", "lbm_reconstruction", "lbm_viscous", "lbm_dirichlet_profile", "lbm_step",
            "lbm_macroscopic", "lbm_boundary_state", "lbm_diagnostics", "lbm_diagnostics_noalloc", "lbm_diag_every", "lbm_state_bytes", "lbm_save",
            "lbm_restore", "lbm_steps_done", "lbm_set_kernel_timing", "lbm_bulk_kernel_time",
            "lbm_tape_bytes", "lbm_record", "lbm_adjoint", "lbm_lattice_info", "lbm_last_error", "lbm_destroy"]
@@ -59,6 +59,7 @@ def load():
     L = ctypes.CDLL(LIB_PATH)
     L.lbm_workspace_bytes.restype = ctypes.c_size_t
     L.lbm_workspace_bytes.argtypes = [ctypes.POINTER(Config)]
+    L.lbm_steps_per_pass.argtypes = [ctypes.POINTER(Config)]
     L.lbm_init.argtypes = [ctypes.POINTER(Config), _vp, ctypes.c_size_t, _vp, _vp, _vp, _vp, _vp,
                            ctypes.POINTER(_vp)]
     L.lbm_cbc_params.argtypes = [_vp, ctypes.c_int, ctypes.POINTER(Relax)]
@@ -115,6 +116,11 @@ def make_config(stencil, nx, ny, tau, bc, precision="fp64"):
 
 def workspace_bytes(cfg):
     return load().lbm_workspace_bytes(ctypes.byref(cfg))
+
+
+def steps_per_pass(cfg):
+    """2 where step() takes two steps per pass over the populations, else 1 (0: invalid)."""
+    return load().lbm_steps_per_pass(ctypes.byref(cfg))
 
 
 class LBM:
