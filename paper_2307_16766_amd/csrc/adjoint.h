@@ -514,6 +514,22 @@ __device__ void adj_chunk(const AdjArgs& g, const SideDev& sd, int side, int blk
 #pragma unroll
         for (int i = 0; i < Q; ++i) nux[i] = v1[(unsigned long long)i * a.pitch];
     }
+    // NEEP: lambda^{n+1} of the layers of the owned rows, M lanes of a wavefront a row, requested here as
+    // well: written by k_adj_bulk into other XCDs' caches, they are a round trip to memory, and the M layers
+    // one after the other after the barrier below made this kernel 42 us (D2Q37, 64 x 47, NEEP sides normal
+    // to y; requested here, at once: 19)
+    const bool neep = sd.meso == 1 && g.neep[side];
+    constexpr int GW = 64 / M;   // rows per wavefront
+    static_assert(4 * GW >= NR - 2 * H, "every owned row has its lanes");
+    const int nl = tid & 63, nq = nl % M, nr = (tid >> 6) * GW + nl / M;
+    const bool nact = neep && nl < GW * M && nr < r1 - r0;
+    double nlam[Q];
+    if (nact) {
+        int x, y; side_node(sd, nq + 1, r0 + nr, x, y);
+        const double* v1 = g.V1 + pix<Q>(a.pitch, 0, x, y);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) nlam[i] = v1[(unsigned long long)i * a.pitch];
+    }
     double cval = 0.0;
     // this work-group's running sums of the parameter adjoints, added to at the end
     const double acc0 = tid < 2 ? g.acc[blk * 2 + tid] : 0.0;
@@ -560,19 +576,20 @@ __device__ void adj_chunk(const AdjArgs& g, const SideDev& sd, int side, int blk
     // pulled at x_f, so the adjoint of that g gets (1 - omega)(Lambda - phi . GM), Lambda = the sum
     // of lambda^{n+1} over the layers, GM = (dm/dM)^T (df^eq/dm)^T Lambda at the strip's moments;
     // k_adj_bulk adds it where it pulls from x_f (owned rows; the layers are read-only here)
-    if (sd.meso == 1 && g.neep[side]) {
+    if (neep) {
         const double cn = 1.0 - a.omega;
         double* nb = g.neep[side];
-        for (int e = tid; e < r1 - r0; e += blockDim.x) {
-            const int rr = r0 + e, l2 = H + e;
-            double lam[Q];
+        if (M > 1) {
 #pragma unroll
-            for (int i = 0; i < Q; ++i) lam[i] = 0.0;
-            for (int q = 1; q <= M; ++q) {
-                int x, y; side_node(sd, q, rr, x, y);
-#pragma unroll
-                for (int i = 0; i < Q; ++i) lam[i] += g.V1[pix<Q>(a.pitch, i, x, y)];
+            for (int i = 0; i < Q; ++i) {
+                double v = nlam[i];
+                for (int q = 1; q < M; ++q) v += __shfl_down(nlam[i], q, 64);
+                nlam[i] = v;
             }
+        }
+        if (nact && nq == 0) {
+            const double* lam = nlam;
+            const int rr = r0 + nr, l2 = H + nr;
             double G[4], GM[4];
             feq_vjp<Q>(&sXp[(l2 * MS) * 4], lam, G);
             mom_vjp<Q>(&sXp[(l2 * MS) * 4], G, GM);
