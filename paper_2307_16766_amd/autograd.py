@@ -27,7 +27,11 @@ class ThermalLBMFunction(torch.autograd.Function):
             sim.set_relax(s, sigma=sg, alpha=al, **relax)
         if spec.get("visc"):
             sim.set_viscous(-1, spec["visc"])
-        sim.record(spec["nsteps"], spec.get("every", 50))
+        if spec.get("record", True):
+            sim.record(spec["nsteps"], spec.get("every", 50))
+        else:   # no gradient can be asked for: the same steps, bit for bit, without what a sweep needs
+            sim.check_record(spec["nsteps"], spec.get("every", 50))
+            sim.step(spec["nsteps"])
         out = torch.stack(sim.macroscopic())
         ctx.sim = sim
         ctx.relax_sides = relax_sides
@@ -52,6 +56,7 @@ def simulate(sigma, alpha, rho0, ux0, uy0, T0, *, stencil, nx, ny, tau, bc, nste
              relax=None, visc=None):
     """Final (rho, ux, uy, T) after nsteps steps, differentiable with respect to sigma, alpha
     (0-d tensors) and the initial fields ((ny, nx) tensors on the GPU)."""
+    record = torch.is_grad_enabled() and any(getattr(t, "requires_grad", False) for t in (sigma, alpha, rho0, ux0, uy0, T0))
     spec = dict(stencil=stencil, nx=nx, ny=ny, tau=tau, bc=list(bc), nsteps=nsteps, every=every,
-                precision=precision, relax=relax or {}, visc=visc)
+                precision=precision, relax=relax or {}, visc=visc, record=record)
     return ThermalLBMFunction.apply(sigma, alpha, rho0, ux0, uy0, T0, spec)

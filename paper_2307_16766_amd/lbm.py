@@ -259,6 +259,14 @@ class LBM:
     def tape_bytes(self, nsteps, every):
         return load().lbm_tape_bytes(self.ctx, nsteps, every)
 
+    def check_record(self, nsteps, every=50):
+        """Raise what record() would raise for these arguments, without recording."""
+        if self.tape_bytes(nsteps, every) == 0:
+            raise LBMError(LBM_E_ARG, "invalid nsteps / every")
+        rc = load().lbm_record(self.ctx, nsteps, every, None, 0)   # refused at the missing tape at the latest
+        if rc != LBM_E_ARG:
+            self._check(rc)
+
     def record(self, nsteps, every=50):
         """Advance nsteps steps from the initial state, keeping a checkpoint every `every` steps
         in a device tape (owned here) for adjoint()."""
