@@ -495,14 +495,15 @@ template <int Q>
 __device__ __forceinline__ void visc_moments(const SideDev& s, const double* d, double tau, double* o6) {
     double rm1, u, v, th;
     moments_dev<Q, double>(d, rm1, u, v, th);
-    double fn[Q];
-    feq_each<Q, double>(rm1, u, v, th, [&](int i, double w, double h) { fn[i] = d[i] - w * h; });
+    double fe[Q];
+    feq_dev<Q, double>(rm1, u, v, th, fe);
     const double fac = 1.0 - 0.5 / tau;
     double pxx = 0, pxy = 0, pyy = 0, qx = 0, qy = 0;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         const double c0 = cx<Q>(i), c1 = cy<Q>(i);
-        pxx -= c0 * c0 * fn[i]; pxy -= c0 * c1 * fn[i]; pyy -= c1 * c1 * fn[i];
+        const double fn = d[i] - fe[i];
+        pxx -= c0 * c0 * fn; pxy -= c0 * c1 * fn; pyy -= c1 * c1 * fn;
         const double dx = c0 - u, dy = c1 - v;
         const double e = (wt<Q>(i) + d[i]) * (dx * dx + dy * dy);
         qx += e * dx; qy += e * dy;
