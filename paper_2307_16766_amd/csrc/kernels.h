@@ -9,7 +9,9 @@
 //   region : two parity copies of the boundary solver state (FP64): per characteristic side
 //            U_b[M][len][4], the bulk strip U[MS][len][4] at x_f (and x_f - 1 for M = 1), the
 //            viscous moments [3][len][6] at x_f-M .. x_f-M-2; per corner U_c[4] and the two
-//            inward diagonal bulk nodes [2][4].  Parity p holds time level n with n % 2 = p.
+//            inward diagonal bulk nodes [2][4].  Parity p holds the time levels n with n % 2 = p (n counted
+//            from the initial or the restored state); a pass of two steps exchanges the two copies,
+//            as it exchanges the population buffers, so that this holds after it too.
 // One time step n -> n+1 is one launch of k_step: its first work-groups each take a chunk of
 // rows of a boundary side (re-pull of the strip from A, RK4 of the characteristic system in
 // LDS, equilibrium populations of the M boundary layers of B); the remaining work-groups each

@@ -217,9 +217,11 @@ __device__ __forceinline__ void feq_dev(R rm1, R ux, R uy, R th, R* fe) {
 // as their difference is what must not be rounded at the size of d; everything after them splits into
 // the pair's even part e = x_+ + x_- and odd part o = x_+ - x_-.  The invariants of the increments are
 // sums over pairs of e (one sum per speed group gives mass and energy) and of c o, and the projection
-// of a member is be_g +- r_p.  That is about 26 instructions a pair instead of 32.  The FP32 passes
-// issue as many VALU cycles as their memory traffic allows: 20 steps of D2Q37 on 4096 x 2048 went from
-// 5998 to 5896 us, on 512 x 512 from 405 to 398 us; errors against 64 bits stayed (ratio 0.99).
+// of a member is be_g +- r_p.  That is about 26 instructions a pair instead of 32, for the passes of two
+// steps, where memory and the vector ALU are both near their rates: 20 steps of D2Q37 on 4096 x 2048
+// went from 5998 to 5896 us.  Single steps on small grids gain nothing (512 x 512: 397 us with either;
+// 256 x 256 14.3 us a step against 13.5 member by member, by registers and code in the boundary path), but
+// a step has to have the same bits in both.  Errors against 64 bits stayed (ratio 0.99).
 template <int Q>
 __device__ __forceinline__ void collide_pairs(float* d, float omega) {
     using L = Lat<Q>;

@@ -1,8 +1,10 @@
 // lbm.hip -- host side of the C ABI declared in include/lbm.h (liblbm_hip.so, gfx950).
 //
 // The library owns no device memory: the caller's workspace is carved into two population
-// buffers, two parity copies of the boundary solver state, the Dirichlet profiles and the
-// diagnostics scratch.  One step is one kernel launch (k_step) on the caller's stream.
+// buffers, two parity copies of the boundary solver state, the Dirichlet profiles, the diagnostics
+// scratch and, on open grids that take two steps per pass, a third copy of the boundary state (the
+// level between the two) and the band buffers.  One step is one kernel launch (k_step) on the caller's
+// stream; a pass of two steps is k_pair, on open grids behind two launches of k_bnd (launch_pair).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

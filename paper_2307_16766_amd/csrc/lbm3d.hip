@@ -223,7 +223,11 @@ int launch_step3(lbm3d_ctx* c) {
         // chain each) take at most four rounds of the 256 CUs: beside the four stage launches and k3_final
         // it takes 16 against 33 us on 61 x 47 rows a face (FP64), 19 against 34 on 64 x 128, 54 against 65 on
         // 192 x 128 (768 work-groups), but 139 against 129 on 256 x 256 (2048), where the stages keep the
-        // memory busy.
+        // memory busy.  Whole steps of 14 nodes between the faces, stages against tiles, FP64: 160 x 160 rows
+        // (800 work-groups) 250.2 : 248.7 us, 176 x 176 (968) 294.5 : 288.5, 12 x 2048 (1024) 231.9 : 231.3, 8 x
+        // 4096 (1024) 294.2 : 285.3, 192 x 170 (1056) 308.3 : 312.1, 208 x 208 (1352) 402.4 : 409.2; FP32 the same
+        // (1.01, 1.01, 1.02, 1.02, 0.99, 1.01).  Thin faces, whose tiles hold few rows, gain as well (4 x 64 rows
+        // 43.4 : 29.7, 4 x 1024 71.8 : 56.5, 9 x 1024 109.6 : 106.1).
         const int ntile = ((a.ny + RK3_T - 1) / RK3_T) * ((a.nz + RK3_T - 1) / RK3_T);
         const bool tiled = 2 * ntile <= 4 * 256;
         if (c->cfg.bc[0] != LBM_BC_ZG || c->cfg.bc[1] != LBM_BC_ZG) {

@@ -23,13 +23,14 @@
 // from n + 1 to n + 2.  A band holds the BW = 3 M + 3 nodes next to a side, enough for every pull of
 // the boundary solve (x_f - M - 2 - M is the innermost node it reads).  Layers of Dirichlet sides
 // are the same at every level and are read from A itself.
-// What bounds it: in FP64 HBM (4.5-4.8 TB/s of useful traffic; the same loads and stores without the
-// collisions take 85 % of the time), in FP32 D2Q37 the vector ALU (about 680 instructions per node
-// and step: the pass without its loads and stores takes 60 % of the time).  Halo columns and rows
-// cost little traffic: HBM reads 1.06x, writes 1.01x of one single step's (counters, D2Q37 FP64
-// 4096 x 2048).  Measured per step against the single-step kernel: D2Q37 4096 x 2048 FP64 periodic
-// 820 -> 570 us, FP32 with Dirichlet / LODI-RELAX sides 417 -> 295 us; D2Q17 FP64 1950 x 1950 186 ->
-// 108 us; D2Q9 FP32 2048 x 2048 58 -> 26 us.  Requesting rows two or three ahead changed nothing (the
+// What bounds it: memory.  A pass over a periodic 4096 x 2048 takes 493 us in FP32 D2Q37, 482 without the
+// collisions and 400 without the global loads and stores (about 680 vector instructions per node and
+// step beside the LDS rings); in FP64 935, 940 and 645; D2Q17 FP64 on 1950 x 1950 212, 206 and 94.  Halo
+// columns and rows cost little traffic: of the algorithmic bytes of one single step HBM reads 1.08 and
+// writes 1.05 times in FP32, 1.07 and 1.01 in FP64 (counters, D2Q37 4096 x 2048 with open sides).
+// Measured per step against the single-step kernel: D2Q37 4096 x 2048 FP64 periodic 820 -> 468 us, FP32
+// with Dirichlet / LODI-RELAX sides 417 -> 277 us; D2Q17 FP64 1950 x 1950 186 -> 106 us; D2Q9 FP32 2048 x 2048
+// 58 -> 26 us.  Requesting rows two or three ahead changed nothing (the
 // loads are not the bound), tiles of half the columns with two work-groups per CU are slower (more
 // halo), unaligned output tiles too (partial lines).
 #pragma once
