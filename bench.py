@@ -29,11 +29,9 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0
 TIMED_EVERY = 10        # kernel-timing stride inside the timed region (see run_gpu)
-STEPS_PER_PASS = 2      # lbm_step on NX x NY (every stencil and precision run here): a pass moves the
-                        # bytes of one step for two
 NX, NY = 4096, 2048
 Q = 37
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_step_d2q37_fp32_4096x2048_traffic.md")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_pair_d2q37_4096x2048_traffic.md")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2307_16766_amd", "csrc", n) for n in ("kernels.h", "lattice.h", "pair.h")]
 
 
@@ -87,6 +85,7 @@ def run_gpu(precision, steps, warmup, q=Q, tau=None):
     kms, launches = g.bulk_kernel_time()
     g.set_kernel_timing(False)
     diag = g.diagnostics()
+    cfg = g.cfg
     g.close()
     del g
     torch.cuda.empty_cache()
@@ -95,8 +94,10 @@ def run_gpu(precision, steps, warmup, q=Q, tau=None):
     # stream), so the smaller of the two is the pass's share per step
     bracketed_ms = kms / max(launches, 1)
     kernel_ms = min(bracketed_ms, step_ms)
-    gbps = bytes_per_launch / (STEPS_PER_PASS * kernel_ms * 1e-3) / 1e9
+    per_pass = lbm.steps_per_pass(cfg)   # a pass moves the bytes of one step for two
+    gbps = bytes_per_launch / (per_pass * kernel_ms * 1e-3) / 1e9
     return {
+        "steps_per_pass": per_pass,
         "ms_per_step": step_ms,
         "mlups": NX * NY / (step_ms * 1e-3) / 1e6,
         "bulk_kernel_ms": kernel_ms,
@@ -357,8 +358,8 @@ def cpu_baseline(steps=None):
 
 
 def traffic_from_profile():
-    """HBM bytes per bulk launch from the committed rocprofv3 counter summary, if it was taken on
-    the current kernel sources (else None)."""
+    """HBM bytes per pass (k_pair and its two k_bnd, FP32) from the committed rocprofv3 counter summary,
+    if it was taken on the current kernel sources (else None)."""
     if not os.path.exists(TRAFFIC_FILE):
         return None
     vals = {}
@@ -494,10 +495,11 @@ def main():
             "unit": "GB/s",
             "frac": r32["bulk_frac"],
             "traffic": traffic,
-            "kernel": "k_pair<37,float> with k_bnd (one pass: two steps of bulk and boundary)",
-            "steps_per_launch": STEPS_PER_PASS,
-            "kernel_ms": STEPS_PER_PASS * r32["bulk_kernel_ms"],
-            "kernel_ms_bracketed": STEPS_PER_PASS * r32["bulk_kernel_ms_bracketed"],
+            "kernel": "k_pair<37,float> with k_bnd (one pass: two steps of bulk and boundary)" if r32["steps_per_pass"] == 2
+                      else "k_step<37,float> (bulk tiles + boundary chunks, one launch per step)",
+            "steps_per_launch": r32["steps_per_pass"],
+            "kernel_ms": r32["steps_per_pass"] * r32["bulk_kernel_ms"],
+            "kernel_ms_bracketed": r32["steps_per_pass"] * r32["bulk_kernel_ms_bracketed"],
             "bytes_per_launch": r32["bulk_bytes_per_launch"],
         },
         "fp64": None if r64 is None else {
