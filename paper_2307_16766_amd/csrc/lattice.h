@@ -161,15 +161,16 @@ __device__ __forceinline__ void feq_group(int g, R u2, R th, R& C0, R& C1, R& D0
         D0 = R(1);
     }
 }
-// H - 1 of both members of a pair with a = xi.u/cs: E + a O and E - a O
+// H - 1 of both members of a pair, E + a O and E - a O with a = xi.u/cs = b / cs (D2Q9 adds b / cs without
+// rounding it first: its FP32 errors are 8 % larger otherwise)
 template <int Q, typename R>
-__device__ __forceinline__ void feq_pair(R a, R C0, R C1, R D0, R& hp, R& hm) {
+__device__ __forceinline__ void feq_pair(R b, R C0, R C1, R D0, R& hp, R& hm) {
     using L = Lat<Q>;
-    const R a2 = a * a;
+    const R ics = R(1.0 / L::cs), a = b * ics, a2 = a * a;
     if (L::order == 2) {
         const R E = C0 + C1 * a2;
-        hp = E + a;
-        hm = E - a;
+        hp = E + b * ics;
+        hm = E - b * ics;
     } else {
         const R E = L::order == 4 ? C0 + a2 * (C1 + a2 * R(1.0 / 24.0)) : C0 + a2 * C1;
         const R O = D0 + a2 * R(1.0 / 6.0);
@@ -192,9 +193,8 @@ __device__ __forceinline__ void feq_each(R rm1, R ux, R uy, R th, F&& f) {
 #pragma unroll
     for (int p = 1; p <= L::NP; ++p) {
         const int g = L::grp(p);
-        const R a = (R(L::pcx(p)) * vx + R(L::pcy(p)) * vy) * ics;
         R hp, hm;
-        feq_pair<Q, R>(a, C0[g], C1[g], D0[g], hp, hm);
+        feq_pair<Q, R>(R(L::pcx(p)) * vx + R(L::pcy(p)) * vy, C0[g], C1[g], D0[g], hp, hm);
         f(p, R(L::wg(g)), rm1 + rho * hp);
         f(p + L::NP, R(L::wg(g)), rm1 + rho * hm);
     }
@@ -241,9 +241,8 @@ __device__ __forceinline__ void collide_pairs(float* d, float omega) {
 #pragma unroll
     for (int p = 1; p <= NP; ++p) {
         const int g = L::grp(p);
-        const float a = (float(L::pcx(p)) * vx + float(L::pcy(p)) * vy) * ics;
         float hp, hm;
-        feq_pair<Q, float>(a, C0[g], C1[g], D0[g], hp, hm);
+        feq_pair<Q, float>(float(L::pcx(p)) * vx + float(L::pcy(p)) * vy, C0[g], C1[g], D0[g], hp, hm);
         const float w = float(L::wg(g));
         x[p] = w * (rm1 + rho * hp) - d[p];
         x[p + NP] = w * (rm1 + rho * hm) - d[p + NP];
